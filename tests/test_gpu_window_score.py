@@ -1,0 +1,53 @@
+"""Window scoring (SnapKV's scores and H2O's chunk scores) where its two passes
+can go wrong: key parts of a page or two, row blocks that are nearly empty, and
+logits whose exponentials leave the range of an fp32 sum without a moving
+reference, in every combination against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import snapkv
+from tests.oracle_bridge import assert_scores_close, f64, gpu_unit, oracle_unit
+from tests.test_gpu_snapkv import DEV, _call
+from workloads import isolated_units, observation_queries, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def se():
+    import paper_2609_39068_amd as m
+    assert torch.cuda.is_available()
+    return m
+
+
+@pytest.mark.parametrize("shift", [0.0, -100.0, 150.0])   # c*z about 0, -100 (all sums underflow), +150 (they overflow)
+@pytest.mark.parametrize("G,window,d,lengths", [
+    (1, 8, 128, [40, 4001]),          # 8 rows: half a row tile, many parts beside a unit of three pages
+    (4, 9, 64, [523, 64]),            # 36 rows: the second size of row block
+    (4, 17, 128, [300, 2050]),        # 68 rows: the third, nearly half empty
+    (1, 129, 128, [400, 1601]),       # two blocks, one row in the second
+    (8, 33, 64, [777, 300]),          # 264 rows: four blocks, one empty, one of 8 rows
+    (8, 65, 128, [1040, 900]),        # 520 rows: eight blocks
+])
+def test_pooled_scores(se, G, window, d, lengths, shift):
+    host = isolated_units(lengths, max_pages=-(-max(lengths) // 16) + 1, head_dim=d, seed=G + window, num_kv_heads=1)
+    q = observation_queries(len(lengths), window, G, d, seed=window).float()
+    u = torch.randn(d, generator=torch.Generator().manual_seed(1))
+    u = u / u.norm()
+    scale = float(np.float32(1.0 / np.sqrt(d)))
+    # every query gains 8 u, every key the multiple of u that moves c*z by `shift`
+    q = (q + 8.0 * u).to(torch.bfloat16)
+    host.kv_pool[:, 0] = (host.kv_pool[:, 0].float() + shift / (8.0 * scale * 1.4427) * u).to(torch.bfloat16)
+    budget = window
+    want = {}
+    for i, L in enumerate(lengths):
+        if L > budget:
+            st = oracle_unit(host, i)
+            want[i] = snapkv.compact_prompt(st, f64(q[i]), window, 5, budget, scale)["s"]
+    gs = to_device(host, DEV)
+    _, _, err = _call(se, gs, 1, G, q.to(DEV), window, 5, scale, budget, se.SE_SNAPKV_SCORE_ONLY)
+    assert err == 0
+    for i, s in want.items():
+        # logits of magnitude m carry about m * 2^-22 of error in fp32 (128 products), 4e-5 here: below the 1e-3 of the scores
+        assert_scores_close(gpu_unit(gs, i)["u"], s, f"unit {i}")
