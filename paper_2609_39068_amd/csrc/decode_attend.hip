@@ -496,7 +496,7 @@ __device__ __forceinline__ bool finish_steady_strided(const AttendParams& p, con
   }
   __syncthreads();
   const int victim = bc[0];
-  store_scores(victim);
+  store_scores(victim == mover ? -1 : victim);
   move_newest<D>(p, g, lds_bt[victim >> 4], victim, lds_bt[mover >> 4], mover, bc[1], bc_u);
   if (tid == 0) {
     p.lengths[g.unit] = p.budget;
@@ -1406,8 +1406,55 @@ __global__ __launch_bounds__(kOrderThreads) void unit_order_kernel(const int32_t
   for (int u = tid; u < num_units; u += kOrderThreads) order[atomicAdd(&cnt[bin_of(u)], 1)] = u;
 }
 
-// Second pass when a unit is split over several work-groups: combines the
-// partials (m, l, o) in split order, writes out and lse, then finishes the unit.
+// Second pass when a unit is split over several work-groups: the partials
+// (m, l, o) combined in split order into out and lse, and the unit's final (m, 1/l)
+// per head into fin_m / fin_il.  Records are loaded in unconditional batches
+// (past the last split they re-read it and weigh nothing): one at a time, 32
+// splits took 17 us of dependent latencies, most of the pass.
+template <int NT, int D, int G>
+__device__ __forceinline__ void combine_unit(const AttendParams& p, const UnitGeom& g, float* fin_m, float* fin_il) {
+  constexpr int MB = 16, OB = 8;  // records in flight
+  const int Hq = p.hkv * G;
+  const int n_act = min(p.n_split, ceil_div_dev(g.n_visit, p.pps));
+  const float* part_u = p.part + (size_t)g.unit * p.n_split * G * (D + 2);
+  for (int idx = threadIdx.x; idx < G * D; idx += NT) {
+    const int h = idx / D;
+    const int c = idx - h * D;
+    auto rec = [&](int s) { return part_u + ((size_t)min(s, n_act - 1) * G + h) * (D + 2); };
+    float m = -INFINITY;
+    for (int s = 0; s < n_act; s += MB) {
+      float v[MB];
+#pragma unroll
+      for (int k = 0; k < MB; ++k) v[k] = rec(s + k)[0];
+#pragma unroll
+      for (int k = 0; k < MB; ++k) m = fmaxf(m, v[k]);
+    }
+    float o = 0.f, l = 0.f;
+    for (int s = 0; s < n_act; s += OB) {
+      float vm[OB], vl[OB], vo[OB];
+#pragma unroll
+      for (int k = 0; k < OB; ++k) {
+        const float* r = rec(s + k);
+        vm[k] = r[0];
+        vl[k] = r[1];
+        vo[k] = r[2 + c];
+      }
+#pragma unroll
+      for (int k = 0; k < OB; ++k) {
+        const float f = vm[k] == -INFINITY || s + k >= n_act ? 0.f : fast_exp2(vm[k] - m);
+        o += vo[k] * f;
+        l += vl[k] * f;
+      }
+    }
+    p.out[((size_t)g.req * Hq + g.kvh * G + h) * D + c] = o / l;
+    if (c == 0) {
+      if (p.lse != nullptr) p.lse[(size_t)g.req * Hq + g.kvh * G + h] = (m + __log2f(l)) * kLn2;
+      fin_m[h] = m;
+      fin_il[h] = 1.f / l;
+    }
+  }
+}
+
 constexpr int kCombineThreads = 512;
 
 template <int D, int G>
@@ -1419,30 +1466,47 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(const A
     if (threadIdx.x == 0) set_error(p.dev_err, SE_DEVERR_BAD_LENGTH);
     return;
   }
-  const int Hq = p.hkv * G;
-  const int n_act = min(p.n_split, ceil_div_dev(g.n_visit, p.pps));
-  const float* part_u = p.part + (size_t)g.unit * p.n_split * G * (D + 2);
-  for (int idx = threadIdx.x; idx < G * D; idx += blockDim.x) {
-    const int h = idx / D;
-    const int c = idx - h * D;
-    float m = -INFINITY;
-    for (int s = 0; s < n_act; ++s) m = fmaxf(m, part_u[((size_t)s * G + h) * (D + 2)]);
-    float o = 0.f, l = 0.f;
-    for (int s = 0; s < n_act; ++s) {
-      const float* rec = part_u + ((size_t)s * G + h) * (D + 2);
-      const float f = rec[0] == -INFINITY ? 0.f : fast_exp2(rec[0] - m);
-      o += rec[2 + c] * f;
-      l += rec[1] * f;
-    }
-    p.out[((size_t)g.req * Hq + g.kvh * G + h) * D + c] = o / l;
-    if (c == 0) {
-      if (p.lse != nullptr) p.lse[(size_t)g.req * Hq + g.kvh * G + h] = (m + __log2f(l)) * kLn2;
-      fin_m[h] = m;
-      fin_il[h] = 1.f / l;
-    }
-  }
+  combine_unit<kCombineThreads, D, G>(p, g, fin_m, fin_il);
   __syncthreads();
   finish_unit<kCombineThreads, G, false, float>(p, g, fin_m, fin_il, nullptr, nullptr, 0);
+}
+
+// The same for an H2O step whose units are at most one slot over the budget
+// (the length bound says so): the score update and the one-slot eviction in
+// this pass too, instead of a general eviction kernel after it (8 units at a
+// budget of 2048: combine 10 + eviction 32 us before).  A unit whose recent
+// window is not the run of its newest positions evicts by the general selection
+// here.
+constexpr int kFinishThreads = 1024;
+
+template <int D, int G>
+__global__ __launch_bounds__(kFinishThreads, 4) void decode_finish_kernel(const AttendParams p) {
+  constexpr int NT = kFinishThreads;
+  __shared__ float fin_m[G];
+  __shared__ float fin_il[G];
+  __shared__ int lds_bt[kMaxBudget / kPage + 1];
+  SE_EVICT_SCRATCH(NT, esc);
+  const UnitGeom g = unit_geom(p, blockIdx.x);
+  if (g.bad) {
+    if (threadIdx.x == 0) set_error(p.dev_err, SE_DEVERR_BAD_LENGTH);
+    return;
+  }
+  const bool steady = g.Lp == p.budget + 1 && g.Lp <= kMaxBudget;
+  if (steady) {  // at most kMaxBudget / kPage pages
+    const int32_t* bt = p.block_table + (size_t)g.unit * p.max_pages;
+    for (int i = threadIdx.x; i < g.n_visit; i += NT) lds_bt[i] = bt[i];
+  }
+  combine_unit<NT, D, G>(p, g, fin_m, fin_il);
+  __syncthreads();
+  bool general;
+  if (steady) {
+    const size_t ubase_p = (size_t)g.unit * p.n_visit_max;
+    const WeightSrc<float> wsrc{nullptr, nullptr, p.pbuf + ubase_p * kPage * G, p.mref + ubase_p * G, 0};
+    general = finish_steady_strided<NT, G, D, float>(p, g, fin_m, fin_il, lds_bt, wsrc, esc);
+  } else {
+    general = finish_unit<NT, G, true, float>(p, g, fin_m, fin_il, nullptr, nullptr, 0);
+  }
+  if (__builtin_expect(general, false)) evict_in_epilogue<NT, D>(p, g, esc);
 }
 
 // With a split, the combine pass updates the scores and publishes the appended
@@ -1485,9 +1549,13 @@ static void launch_attend(const AttendParams& prm, int grid, bool wide, hipStrea
   else
     launch_attend_nt<D, G, kAttendThreads>(prm, grid, stream);
   if (prm.n_split > 1) {
+    const int units = grid / prm.n_split;
+    if (prm.evict && prm.max_len - 1 <= prm.budget) {
+      hipLaunchKernelGGL((decode_finish_kernel<D, G>), dim3(units), dim3(kFinishThreads), 0, stream, prm);
+      return;
+    }
     AttendParams cp = prm;
     cp.evict = 0;
-    const int units = grid / prm.n_split;
     hipLaunchKernelGGL((decode_combine_kernel<D, G>), dim3(units), dim3(kCombineThreads), 0, stream, cp);
     if (prm.evict) {
       EvictParams ep;
@@ -1525,7 +1593,8 @@ size_t se_attend_workspace_bytes(int32_t num_units, int32_t max_len, int32_t max
                                  int32_t q_per_kv, int32_t head_dim, int32_t top_k) {
   if (num_units <= 0 || max_len <= 0 || max_pages <= 0 || q_per_kv <= 0 || head_dim <= 0)
     return 0;
-  const SplitShape s = split_shape(num_units, attend_n_visit(max_len, max_pages, top_k));
+  const int n_visit = attend_n_visit(max_len, max_pages, top_k);
+  const SplitShape s = split_shape(num_units, n_visit, attend_wide(num_units, n_visit) ? 256 : 512);
   return attend_ws_layout(num_units, s, q_per_kv, head_dim).total;
 }
 

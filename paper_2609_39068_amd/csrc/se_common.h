@@ -48,15 +48,35 @@ struct SplitShape {
 
 // resident: work-groups that fit the chip at once (512: two 8-wavefront
 // work-groups on each of 256 compute units; 256: one 16-wavefront one).
+// The number of splits is the one whose rounds of work-groups stream the fewest
+// pages one after the other, a work-group's prologue and epilogue counted as
+// kFixedPages: 224 units of 513 pages take one split (199 us for an H2O step;
+// two splits would take two rounds, 247), 320 units of 129 pages too (81 us; two
+// splits 103).  Splits cost a second kernel, about 10 us, which a unit
+// streams some kWorthPages pages in: 8 units of 65 pages take 20.5 us whole and
+// 22.5 split, of 129 pages 29.8 whole and 23.8 split, 128 units of 129 pages 46.6
+// and 43.9.
 inline SplitShape split_shape(int num_units, int n_visit, int resident = 512) {
   const int min_pages = 16;          // at least two pages per wavefront
   const int max_group_pages = 1024;  // the page table a work-group stages in LDS
-  int splits = (int)ceil_div(resident, num_units);
-  int by_size = (int)ceil_div(n_visit, min_pages);
-  if (splits > by_size) splits = by_size;
-  if (splits < 1) splits = 1;
-  if (splits < ceil_div(n_visit, max_group_pages)) splits = (int)ceil_div(n_visit, max_group_pages);
-  int pps = (int)ceil_div(n_visit, splits);
+  const int kFixedPages = 16;
+  const int kWorthPages = 60;
+  const int lo = (int)ceil_div(n_visit, max_group_pages);
+  int hi = (int)ceil_div(resident, num_units);
+  hi = hi < (int)ceil_div(n_visit, min_pages) ? hi : (int)ceil_div(n_visit, min_pages);
+  hi = hi > 2 * lo ? hi : 2 * lo;
+  int splits = lo;
+  int64_t best = INT64_MAX;
+  for (int n = lo; n <= hi; ++n) {
+    const int64_t per = ceil_div(n_visit, n);
+    if (n > 1 && lo == 1 && n_visit - per < kWorthPages) continue;
+    const int64_t cost = ceil_div((int64_t)num_units * n, resident) * (per + kFixedPages);
+    if (cost < best) {
+      best = cost;
+      splits = n;
+    }
+  }
+  const int pps = (int)ceil_div(n_visit, splits);
   splits = (int)ceil_div(n_visit, pps);
   return SplitShape{n_visit, splits, pps};
 }

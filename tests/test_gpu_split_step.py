@@ -1,0 +1,68 @@
+"""The H2O step of few units: their attention is split over work-groups and a
+second kernel combines, updates the scores and evicts.  Against the same step
+as two calls (se_decode_attend, then se_evict_compact), bit for bit: both form
+the same scores, and the eviction is exact."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2609_39068_amd.decode as decode
+from workloads import clone_state, isolated_units, to_device
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def se():
+    import paper_2609_39068_amd as m
+    assert torch.cuda.is_available()
+    return m
+
+
+@pytest.mark.parametrize("mode,levels", [("permuted", 0), ("permuted", 3), ("gapped", 0)])
+@pytest.mark.parametrize("G,d,budget,recent", [
+    (4, 128, 1296, 162),    # 82 pages, the page the append opens
+    (1, 64, 1500, 1500),    # the window is the budget
+    (2, 128, 2047, 0),      # no window
+    (8, 128, 4100, 513),    # more slots than threads times four
+    (4, 64, 8191, 100),     # the longest unit of the one-slot eviction
+    (4, 128, 8192, 1000),   # one longer: the general selection
+])
+def test_few_units_match_two_calls(se, G, d, budget, recent, mode, levels):
+    hkv = 2
+    # at the budget, one below it (fills it), far below it, at it again
+    lengths = [budget, budget - 1, budget - 300, budget]
+    P = budget // 16 + 1
+    host = isolated_units(lengths, max_pages=P, head_dim=d, seed=budget + G, num_kv_heads=hkv, position_mode=mode,
+                          score_levels=levels)
+    g = torch.Generator().manual_seed(7)
+    nreq = len(lengths) // hkv
+    results = []
+    steps = 2  # the second step starts from what the first left
+    inputs = [(torch.randn(nreq, hkv * G, d, generator=g).to(torch.bfloat16).to(DEV),
+               torch.randn(nreq, hkv, d, generator=g).to(torch.bfloat16).to(DEV),
+               torch.randn(nreq, hkv, d, generator=g).to(torch.bfloat16).to(DEV),
+               # the next position of a contiguous history; past every other mode's
+               torch.full((nreq,), (budget if mode == "permuted" else 5 * budget + 100) + t, dtype=torch.int32, device=DEV))
+              for t in range(steps)]
+    for fused in (True, False):
+        print(f"G={G} d={d} B={budget} {mode} fused={fused}", flush=True)
+        st = to_device(clone_state(host), DEV)
+        view = se.KVView(st.kv_pool, st.pos_pool, st.score_pool, None, st.block_table, st.lengths, num_kv_heads=hkv)
+        dec = decode.H2ODecoder(view, G, float(np.float32(1 / np.sqrt(d))), budget, recent, budget + 1, DEV, report_freed=True)
+        out = torch.zeros(nreq, hkv * G, d, device=DEV)
+        lse = torch.zeros(nreq, hkv * G, device=DEV)
+        got = []
+        for q, k, v, pos in inputs:
+            dec.step(q, k, v, pos, out, lse, fused=fused)
+            got += [out.clone(), lse.clone(), st.lengths.clone(), st.pos_pool.clone(), st.score_pool.clone(), st.kv_pool.clone(),
+                    dec.freed_count.clone()]
+        torch.cuda.synchronize()
+        assert se.se_read_device_errors(dec.dev_err) == 0
+        results.append(got)
+    names = ["out", "lse", "lengths", "pos", "score", "kv", "freed"] * steps
+    assert results[0][2].tolist() == [budget, budget, budget - 299, budget]
+    for n, a, b in zip(names, *results):
+        assert torch.equal(a, b), n
