@@ -10,8 +10,11 @@
 // Selection: omnikv_score_kernel takes the maximum over the request's Hq
 // logit rows (contiguous in the logits layout) for a chunk of slots, coalesced,
 // into the workspace; omnikv_topk_kernel (one 1024-thread work-group per
-// request) copies the request's scores to LDS when they fit (eight loads in
-// flight per thread), finds the b-th largest key by an 8-bit radix selection
+// request) first takes a threshold from a sample of the scores that about
+// twice the budget pass, reads the scores once to list those slots, and selects
+// among them (sampled_topk).  Where a third of the slots or more is selected, or
+// the sample misjudges, it copies the request's scores to LDS when they fit
+// (eight loads in flight per thread), finds the b-th largest key by an 8-bit radix selection
 // over order-preserving keys (ties: lower slot; the histogram replicated over
 // eight LDS copies, so that lanes sharing a digit update different words), and
 // writes the selected slots in increasing order: every thread owns a
@@ -54,6 +57,7 @@ struct OmniSelectParams {
   int32_t max_len;
   int32_t ws_stride;
   int32_t vec4;          // logits rows 16-byte aligned: four slots per load
+  int32_t ws4;           // score rows 16-byte aligned
   float* scores;         // workspace [num_req][ws_stride]
   int32_t* sel;          // [num_req][budget]
   int32_t* dev_err;
@@ -179,8 +183,236 @@ __global__ __launch_bounds__(kOmniScoreThreads) void omnikv_score_kernel(const O
   }
 }
 
+// TopK_b among the slots whose key passes a sampled threshold.  Exact: the
+// threshold only has to leave at least b and at most kOmniCand slots, which the
+// count of them shows; false when it does not (nothing written then).
+//   1. 1024 scores at equal distances; the threshold is about their r-th
+//      largest, r four standard deviations above the expected rank of the b-th
+//      score (binary search over the key bits by ballots, in every wavefront).
+//   2. Every wavefront reads its contiguous share of the scores, 16 bytes per
+//      lane and eight loads in flight, keeps one bit per slot, and lists its
+//      passing slots in LDS (in no particular order).
+//   3. Radix selection over the listed slots' keys, held in registers, as
+//      distances from the threshold: their leading digit then spreads over the
+//      bins, while the plain keys' leading digit (sign and exponent) is nearly one
+//      value and its atomics would serialise.
+//   4. Selected slots and threshold ties as two bitmaps; every thread owns 128
+//      slots of both, so two block scans give the ties taken (lowest slots first) and
+//      the output offsets in slot order.
+// One compute unit reads a request's scores at about 100 GB/s, so one pass over
+// them instead of five is most of it: one request of 130002 slots 268 -> 30 us, 32
+// of 32769 slots 31 -> 26.
+constexpr int kOmniSample = 1024;
+constexpr int kOmniSampledMin = 4096;  // slots: below, the LDS copy is as fast
+constexpr int kOmniCand = 16384;        // listed slots
+constexpr int kOmniSampledMax = 131072;  // slots: 128 bits per lane and per thread
+struct OmniSampledLds {
+  uint32_t sample[kOmniSample];
+  int list[kOmniCand];
+  uint32_t above[kOmniSampledMax / 32];
+  uint32_t equal[kOmniSampledMax / 32];
+  int wave_count[kOmniTopkThreads / kWave];
+  uint32_t wave_max[kOmniTopkThreads / kWave];
+};
+
+__device__ __forceinline__ bool sampled_topk(const float* sc, int L, int b, int32_t* out, OmniSampledLds& m, unsigned* hist,
+                                             int* scan, int* bcast) {
+  constexpr int NT = kOmniTopkThreads, NW = NT / kWave, KC = kOmniCand / NT;
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  const int wave = tid / kWave;
+  // ---- 1. the threshold
+  m.sample[tid] = float_key(sc[(int)((int64_t)tid * L / kOmniSample)]);
+#pragma unroll
+  for (int i = 0; i < kOmniSampledMax / 32 / NT; ++i) {
+    m.above[tid + i * NT] = 0u;
+    m.equal[tid + i * NT] = 0u;
+  }
+  for (int i = tid; i < kOmniHistCopies * 257; i += NT) hist[i] = 0u;
+  __syncthreads();
+  const float mean = (float)kOmniSample * (float)b / (float)L;
+  const int r = min(kOmniSample, (int)(mean + 4.f * __builtin_sqrtf(mean) + 8.f));
+  uint32_t thr = 0;
+  {
+    uint32_t k[kOmniSample / kWave];
+#pragma unroll
+    for (int j = 0; j < kOmniSample / kWave; ++j) k[j] = m.sample[lane + j * kWave];
+    for (int bit = 31; bit >= 10; --bit) {
+      const uint32_t t = thr | (1u << bit);
+      int n = 0;
+#pragma unroll
+      for (int j = 0; j < kOmniSample / kWave; ++j) n += __popcll(__ballot(k[j] >= t));
+      if (n >= r) thr = t;
+    }
+  }
+  // ---- 2. the passing slots: lane l of a wavefront holds slots c0 + 256 * i + 4 * l .. + 3 in bits
+  // 4 * (i % 8) .. of bits[i / 8]
+  const int C = ceil_div_dev(L, NW * 256) * 256;  // a wavefront's slots, at most 8192
+  const int c0 = wave * C;
+  const int end = min(L, c0 + C);
+  uint32_t bits[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    if (c0 + g * 2048 < end) {
+      float4 v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        v[k] = *reinterpret_cast<const float4*>(sc + min(c0 + g * 2048 + k * 256 + 4 * lane, (L - 1) & ~3));
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int s = c0 + g * 2048 + k * 256 + 4 * lane;
+        const float x[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bits[g] |= (s + e < end && float_key(x[e]) >= thr ? 1u : 0u) << (4 * k + e);
+      }
+    }
+  }
+  const int mine = __popc(bits[0]) + __popc(bits[1]) + __popc(bits[2]) + __popc(bits[3]);
+  int incl = mine;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int y = __shfl_up(incl, o, kWave);
+    if (lane >= o) incl += y;
+  }
+  if (lane == kWave - 1) m.wave_count[wave] = incl;
+  __syncthreads();
+  int at = incl - mine, n = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const int c = m.wave_count[w];
+    if (w < wave) at += c;
+    n += c;
+  }
+  if (n < b || n > kOmniCand) return false;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    uint32_t w = bits[g];
+    while (w != 0) {
+      const int j = __builtin_ctz(w);
+      w &= w - 1;
+      m.list[at++] = c0 + g * 2048 + (j >> 2) * 256 + 4 * lane + (j & 3);
+    }
+  }
+  __syncthreads();
+  // ---- 3. selection among the n listed slots (thread t: entries t + k * NT)
+  uint32_t d[KC];
+  uint32_t dmax = 0;
+#pragma unroll
+  for (int k = 0; k < KC; ++k)
+    if (k * NT < n) d[k] = __float_as_uint(sc[m.list[min(tid + k * NT, n - 1)]]);
+#pragma unroll
+  for (int k = 0; k < KC; ++k)
+    if (k * NT < n) {
+      d[k] = float_key(__uint_as_float(d[k])) - thr;
+      dmax = max(dmax, d[k]);  // entries past the end repeat the last one
+    }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) dmax = max(dmax, (uint32_t)__shfl_xor((int)dmax, o, kWave));
+  if (lane == 0) m.wave_max[wave] = dmax;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) dmax = max(dmax, m.wave_max[w]);
+  unsigned* const my_hist = hist + (tid % kOmniHistCopies) * 257;
+  const int nbits = dmax == 0 ? 1 : 32 - __builtin_clz(dmax);
+  int shift = max(0, nbits - 8);
+  uint32_t prefix = 0;  // the digits fixed so far (d >> shift)
+  int k_rest = b;
+  for (int width = nbits - shift;;) {  // bits of this pass's digit
+#pragma unroll
+    for (int k = 0; k < KC; ++k)
+      if (k * NT < n && tid + k * NT < n && ((uint64_t)d[k] >> (shift + width)) == prefix)
+        atomicAdd(&my_hist[(d[k] >> shift) & ((1u << width) - 1u)], 1u);
+    __syncthreads();
+    if (wave == 0) {
+      // lane l holds digits 255-4l .. 252-4l (descending); inclusive prefix over lanes
+      int c[4], s4 = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        int v = 0;
+#pragma unroll
+        for (int cp = 0; cp < kOmniHistCopies; ++cp) {
+          unsigned* const w = hist + cp * 257 + 255 - 4 * lane - j;
+          v += (int)*w;
+          *w = 0u;
+        }
+        c[j] = v;
+        s4 += v;
+      }
+      int inc = s4;
+#pragma unroll
+      for (int o = 1; o < kWave; o <<= 1) {
+        const int y = __shfl_up(inc, o, kWave);
+        if (lane >= o) inc += y;
+      }
+      int run = inc - s4;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (c[j] > 0 && run < k_rest && run + c[j] >= k_rest) {
+          bcast[0] = 255 - 4 * lane - j;
+          bcast[1] = run;
+          bcast[2] = c[j];
+        }
+        run += c[j];
+      }
+    }
+    __syncthreads();
+    prefix = (prefix << width) | (uint32_t)bcast[0];
+    k_rest -= bcast[1];
+    if (bcast[2] == k_rest || shift == 0) break;
+    width = min(8, shift);
+    shift -= width;
+  }
+  // ---- 4. the selection in slot order
+#pragma unroll
+  for (int k = 0; k < KC; ++k)
+    if (k * NT < n && tid + k * NT < n) {
+      const uint32_t x = d[k] >> shift;
+      const int s = m.list[tid + k * NT];
+      if (x > prefix) atomicOr(&m.above[s >> 5], 1u << (s & 31));
+      else if (x == prefix) atomicOr(&m.equal[s >> 5], 1u << (s & 31));
+    }
+  __syncthreads();
+  uint32_t sel[4], eq[4];
+  int n_eq = 0, tot;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    sel[i] = m.above[4 * tid + i];
+    eq[i] = m.equal[4 * tid + i];
+    n_eq += __popc(eq[i]);
+  }
+  const int eq_before = block_exclusive_scan<NT>(n_eq, scan, &tot);
+  int take = min(max(k_rest - eq_before, 0), n_eq);
+  int n_sel = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int c = __popc(eq[i]);
+    if (take >= c) {
+      sel[i] |= eq[i];
+      take -= c;
+    } else {
+      for (; take > 0; --take) {
+        const uint32_t low = eq[i] & (~eq[i] + 1u);  // the lowest remaining tie
+        sel[i] |= low;
+        eq[i] ^= low;
+      }
+    }
+    n_sel += __popc(sel[i]);
+  }
+  int o = block_exclusive_scan<NT>(n_sel, scan, &tot);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    uint32_t w = sel[i];
+    while (w != 0) {
+      out[o++] = 128 * tid + 32 * i + __builtin_ctz(w);
+      w &= w - 1;
+    }
+  }
+  return true;
+}
+
 __global__ __launch_bounds__(kOmniTopkThreads) void omnikv_topk_kernel(const OmniSelectParams p) {
   __shared__ __attribute__((aligned(16))) float s_sc[kOmniLdsScores];
+  static_assert(sizeof(OmniSampledLds) <= sizeof(s_sc), "the sampled selection shares the scores' buffer");
   __shared__ unsigned s_hist[kOmniHistCopies * 257];
   __shared__ int s_scan[kOmniTopkThreads / kWave + 1];
   __shared__ int s_bcast[4];
@@ -201,6 +433,10 @@ __global__ __launch_bounds__(kOmniTopkThreads) void omnikv_topk_kernel(const Omn
     return;
   }
   const float* gsc = p.scores + (size_t)req * p.ws_stride;
+  if (p.ws4 && L >= kOmniSampledMin && L <= kOmniSampledMax && 3 * b <= L) {
+    if (sampled_topk(gsc, L, b, out, *reinterpret_cast<OmniSampledLds*>(s_sc), s_hist, s_scan, s_bcast)) return;
+    __syncthreads();  // its buffer is free
+  }
   const float* sc = gsc;
   if (L <= kOmniLdsScores) {
     // eight loads in flight per thread (16-byte ones when the rows are aligned);
@@ -686,6 +922,7 @@ extern "C" se_status se_omnikv_select(const se_kv_view* kv, int32_t q_per_kv, co
   p.ws_stride = (int32_t)align_up((size_t)max_len, 64);
   p.vec4 = (reinterpret_cast<uintptr_t>(logits) % 16 == 0 && logits_stride % 4 == 0 &&
             reinterpret_cast<uintptr_t>(ws) % 16 == 0) ? 1 : 0;
+  p.ws4 = reinterpret_cast<uintptr_t>(ws) % 16 == 0 ? 1 : 0;
   p.scores = static_cast<float*>(ws);
   p.sel = sel_slots;
   p.dev_err = dev_err;
