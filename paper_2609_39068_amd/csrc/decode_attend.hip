@@ -70,6 +70,7 @@ struct AttendParams {
   float* lse;
   float* logits;
   int32_t logits_stride;
+  int32_t logits_vec;  // logits rows 16-byte aligned
   float* part;
   float* pbuf;
   float* mref;
@@ -770,11 +771,12 @@ __device__ __forceinline__ void qk_page(const Lanes<D>& ln, const uint4 (&kb)[2 
 
 // Reference update, weight of the lane's pair, its workspace copy, and the
 // weights' broadcast through LDS (the page's PV follows).
-template <int D, int G, typename W>
+// lds_z (kLogits only): the page's logits for store_logits.
+template <int D, int G, bool kLogits, typename W>
 __device__ __forceinline__ void softmax_page(const AttendParams& p, const Lanes<D>& ln,
                                              const PageRef& pr, const float (&z)[kPairs<G>], WaveSoftmax<G>& ws,
-                                             float* lds_pw, int lane, int unit, size_t ubase_p,
-                                             W* lds_w, float* lds_mr, int wcap) {
+                                             float* lds_pw, int lane, size_t ubase_p,
+                                             W* lds_w, float* lds_mr, int wcap, float* lds_z) {
   constexpr int NP = kPairs<G>, GH = kPassHeads<G>;
   constexpr float kBump = 8.0f;  // rescale only when a logit beats the reference by 2^8
   const bool valid = ln.owns && ln.own_row < pr.nrows;
@@ -783,9 +785,7 @@ __device__ __forceinline__ void softmax_page(const AttendParams& p, const Lanes<
 #pragma unroll
   for (int k = 0; k < NP; ++k) {
     z2[k] = valid ? z[k] * p.scale_log2 : -INFINITY;
-    if (p.logits != nullptr && valid)
-      p.logits[((size_t)unit * G + ln.own_head + 4 * k) * p.logits_stride + pr.lp * kPage + ln.own_row] =
-          z[k] * p.scale;
+    if (kLogits && valid) lds_z[(ln.own_head + 4 * k) * kPage + ln.own_row] = z[k] * p.scale;
     need = need || (valid && (z2[k] > ws.m_own[k] + kBump));
   }
   if (__ballot(need) != 0) {
@@ -830,6 +830,46 @@ __device__ __forceinline__ void softmax_page(const AttendParams& p, const Lanes<
     if (ln.owns) lds_pw[ln.own_row * G + hh] = pj[k];
   }
   wave_lds_sync();
+}
+
+// kLogits: pages whose logits a wavefront keeps in LDS (the weight buffer)
+// before it stores them.
+template <int NT, int G>
+constexpr int kLogitsBurst = []() constexpr {
+  int n = 16;
+  while (n * (NT / kWave) * G * kPage > kWeightCap) n /= 2;
+  return n;
+}();
+
+// Stores the logits of the wavefront's pages i0 .. i0 + n - 1 (staged entries
+// entry(i), lds_z [page][head][row]), 16 bytes per lane where the rows allow it:
+// four consecutive pages are 256 consecutive bytes per head, and the wavefronts
+// take their pages in groups of four here.  Stored page by page, 64 bytes per
+// head, the 134 MB of logits of 256 units of 32768 slots cost 250 us on top of
+// 662 us of attention.
+template <int G, typename Entry>
+__device__ __forceinline__ void store_logits(const AttendParams& p, const float* lds_z, const int* lds_lp, int i0, int n,
+                                             int unit, int Lp, int lane, Entry entry) {
+  float* const base = p.logits + (size_t)unit * G * p.logits_stride;  // the unit's rows
+  for (int x = lane; x < G * 4 * ((n + 3) & ~3); x += kWave) {
+    // piece x: its group of four pages, then head, page of the group, four rows
+    const int q = x / (16 * G), y = x - q * (16 * G);
+    const int h = y >> 4, k = 4 * q + ((y >> 2) & 3), r = (y & 3) * 4;
+    if (k < n) {
+      const int s = lds_lp[entry(i0 + k)] * kPage + r;
+      const float4 v = *reinterpret_cast<const float4*>(lds_z + (k * G + h) * kPage + r);
+      float* dst = base + ((size_t)h * p.logits_stride + s);
+      if (p.logits_vec && s + 4 <= Lp) {
+        *reinterpret_cast<float4*>(dst) = v;
+      } else {
+        if (s < Lp) dst[0] = v.x;
+        if (s + 1 < Lp) dst[1] = v.y;
+        if (s + 2 < Lp) dst[2] = v.z;
+        if (s + 3 < Lp) dst[3] = v.w;
+      }
+    }
+  }
+  wave_lds_sync();  // before the next page's logits
 }
 
 // o += P V for one page, the weights read back from LDS.
@@ -931,7 +971,8 @@ __device__ __forceinline__ const int* fused_quest_select(const AttendParams& p, 
 // slots (finish_steady_strided).  Two instantiations, chosen on the host from
 // the step's length bound, since carrying both paths costs the shorter one
 // registers.
-template <int D, int G, int NT, bool kWaveRows, bool kQuest>
+// kLogits: every slot's logits are an output.
+template <int D, int G, int NT, bool kWaveRows, bool kQuest, bool kLogits>
 __global__ __launch_bounds__(NT, 4) void decode_attend_kernel(const AttendParams p) {
   constexpr int NW = NT / kWave;  // wavefronts per work-group
   using LN = Lanes<D>;
@@ -977,7 +1018,9 @@ __global__ __launch_bounds__(NT, 4) void decode_attend_kernel(const AttendParams
   // work-group holds the whole unit); the rest go to the workspace.  The fused
   // Quest selection keeps its results in the same buffer (and never accumulates).
   const bool select = kQuest && p.select;
-  const int wcap = (p.accumulate && p.n_split == 1 && !select) ? kWeightPages<G, W> : 0;
+  // With kLogits it holds the logits of each wavefront's last pages.
+  const int wcap = (p.accumulate && p.n_split == 1 && !select && !kLogits) ? kWeightPages<G, W> : 0;
+  static_assert(!kLogits || (!kQuest && !kWaveRows && kLogitsBurst<NT, G> >= 4), "logits instantiation");
 
   // QK layout: lane = 8*r8 + j8 reads columns [j8*QC, (j8+1)*QC) of rows r8
   // (pass A) and r8 + 8 (pass B).  After the 8-lane reduction, lane j8 < 4
@@ -1093,12 +1136,16 @@ __global__ __launch_bounds__(NT, 4) void decode_attend_kernel(const AttendParams
   const int srank = wave >> 2, wr = wave & 3;
   const int gl = n_grp - 1;  // the last staged entry
   int rbeg = 0, rcnt = 0, max_rcnt = 0, owner_rank = 0, owner_beg = 0;
+  // with kLogits, groups of four consecutive pages per wavefront (store_logits) once every wavefront has two of them
+  const int gs = kLogits && n_grp >= 8 * NW ? 2 : 0;
+  const int gmask = (1 << gs) - 1;
   {
     int cum = 0, b = 0;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       cum += RankWeights<NR>::w[r];
-      const int e = (n_grp * cum + 50) / 100;
+      int e = (n_grp * cum + 50) / 100;
+      if (kLogits && r < NR - 1) e &= ~gmask;
       if (r == srank) {
         rbeg = b;
         rcnt = e - b;
@@ -1111,7 +1158,12 @@ __global__ __launch_bounds__(NT, 4) void decode_attend_kernel(const AttendParams
       b = e;
     }
   }
-  const int n_my = wr < rcnt ? (rcnt - wr + 3) / 4 : 0;
+  // page i of this wavefront is staged entry entry(i): every fourth one, or every fourth group
+  auto entry = [&](int i) -> int {
+    return kLogits ? rbeg + ((i >> gs) << (gs + 2)) + (wr << gs) + (i & gmask) : rbeg + wr + 4 * i;
+  };
+  int n_my = wr < rcnt ? (rcnt - wr + 3) / 4 : 0;
+  if (kLogits && gs != 0) n_my = (rcnt >> 4) * 4 + max(0, min(4, (rcnt & 15) - wr * 4));
 
   // ---- append: the new token's page is the last one visited (the last staged
   // entry, when it is valid); the wavefront that streams it writes the row into
@@ -1121,7 +1173,7 @@ __global__ __launch_bounds__(NT, 4) void decode_attend_kernel(const AttendParams
   {
     const int new_vp = quest ? p.top_k : cur_page;
     const bool mine_new = append && !bad && new_vp >= vbeg && new_vp < vend && gl >= 0 && lds_vp[gl] == new_vp;
-    const int owner_wr = (gl - owner_beg) & 3;
+    const int owner_wr = ((gl - owner_beg) >> gs) & 3;
     if (mine_new && srank == owner_rank && wr == owner_wr) {
       const int ph = lds_phys[gl];
       const int rn = L - cur_page * kPage;
@@ -1161,7 +1213,7 @@ __global__ __launch_bounds__(NT, 4) void decode_attend_kernel(const AttendParams
 
   auto page_ref = [&](int i) -> PageRef {
     PageRef pr;
-    const int gi = rbeg + wr + 4 * i;
+    const int gi = entry(i);
     // wave-uniform by construction: keep them in scalar registers
     pr.vp = __builtin_amdgcn_readfirstlane(lds_vp[gi]);
     pr.lp = __builtin_amdgcn_readfirstlane(lds_lp[gi]);
@@ -1193,30 +1245,40 @@ __global__ __launch_bounds__(NT, 4) void decode_attend_kernel(const AttendParams
     load_k<D>(p, ln, nx1, kbB);
     __builtin_amdgcn_sched_barrier(0);
     load_v<D>(p, ln, cur, vb);
-    for (int i = 0; i < n_my; i += 2) {
+    // with kLogits, bursts of pages whose logits are stored together
+    constexpr int BURST = kLogits ? kLogitsBurst<NT, G> : 1;
+    float* const lds_z = lds_w + wave * (BURST * G * kPage);
+    for (int ib = 0; ib < n_my; ib += BURST) {
+    const int ie = kLogits ? min(n_my, ib + BURST) : n_my;
+    for (int i = kLogits ? ib : 0; i < ie; i += 2) {
       {
         const PageRef nx2 = ref_or_tail(i + 2);
         float z[NP];
         qk_page<D, G>(ln, kbA, lds_q, z);
         load_k<D>(p, ln, nx2, kbA);
-        softmax_page<D, G, W>(p, ln, cur, z, ws, lds_p[wave], lane, unit, ubase_p, lds_wh, lds_mr, wcap);
+        softmax_page<D, G, kLogits, W>(p, ln, cur, z, ws, lds_p[wave], lane, ubase_p, lds_wh, lds_mr, wcap,
+                                       lds_z + (i - ib) * (G * kPage));
         pv_page<D, G>(ln, vb, cur.nrows, ws, lds_p[wave]);
         load_v<D>(p, ln, nx1, vb);
         cur = nx1;
         nx1 = nx2;
       }
-      if (i + 1 >= n_my) break;
+      if (i + 1 >= ie) break;
       {
         const PageRef nx2 = ref_or_tail(i + 3);
         float z[NP];
         qk_page<D, G>(ln, kbB, lds_q, z);
         load_k<D>(p, ln, nx2, kbB);
-        softmax_page<D, G, W>(p, ln, cur, z, ws, lds_p[wave], lane, unit, ubase_p, lds_wh, lds_mr, wcap);
+        softmax_page<D, G, kLogits, W>(p, ln, cur, z, ws, lds_p[wave], lane, ubase_p, lds_wh, lds_mr, wcap,
+                                       lds_z + (i + 1 - ib) * (G * kPage));
         pv_page<D, G>(ln, vb, cur.nrows, ws, lds_p[wave]);
         load_v<D>(p, ln, nx1, vb);
         cur = nx1;
         nx1 = nx2;
       }
+    }
+    if constexpr (!kLogits) break;
+    store_logits<G>(p, lds_z, lds_lp, ib, ie - ib, unit, Lp, lane, entry);
     }
   }
 
@@ -1535,11 +1597,13 @@ inline bool attend_wide(int num_units, int n_visit) {
 template <int D, int G, int NT>
 static void launch_attend_nt(const AttendParams& prm, int grid, hipStream_t stream) {
   if (prm.sel != nullptr)  // Quest: no eviction code, per-wavefront rows are not used
-    hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, false, true>), dim3(grid), dim3(NT), 0, stream, prm);
+    hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, false, true, false>), dim3(grid), dim3(NT), 0, stream, prm);
+  else if (prm.logits != nullptr)
+    hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, false, false, true>), dim3(grid), dim3(NT), 0, stream, prm);
   else if (prm.n_visit_max <= wave_rows_pages<NT, G>())
-    hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, true, false>), dim3(grid), dim3(NT), 0, stream, prm);
+    hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, true, false, false>), dim3(grid), dim3(NT), 0, stream, prm);
   else
-    hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, false, false>), dim3(grid), dim3(NT), 0, stream, prm);
+    hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, false, false, false>), dim3(grid), dim3(NT), 0, stream, prm);
 }
 
 template <int D, int G>
@@ -1660,6 +1724,7 @@ static se_status attend_launch(const se_kv_view* kv, int32_t q_per_kv, const voi
   prm.lse = lse;
   prm.logits = logits;
   prm.logits_stride = logits_stride;
+  prm.logits_vec = reinterpret_cast<uintptr_t>(logits) % 16 == 0 && logits_stride % 4 == 0 ? 1 : 0;
   char* base = static_cast<char*>(ws);
   prm.part = reinterpret_cast<float*>(base + lay.part);
   prm.pbuf = reinterpret_cast<float*>(base + lay.pbuf);

@@ -76,7 +76,8 @@ inline SplitShape split_shape(int num_units, int n_visit, int resident = 512) {
       splits = n;
     }
   }
-  const int pps = (int)ceil_div(n_visit, splits);
+  int pps = (int)ceil_div(n_visit, splits);
+  if (splits > 1) pps = pps + 3 < max_group_pages ? (pps + 3) & ~3 : pps;  // whole 256-byte runs of logits per split
   splits = (int)ceil_div(n_visit, pps);
   return SplitShape{n_visit, splits, pps};
 }
