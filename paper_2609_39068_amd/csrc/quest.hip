@@ -42,6 +42,7 @@ struct QuestParams {
   float* scores;
   int32_t scores_stride;
   int32_t blocks_per_unit;
+  int32_t pages_per_block;  // bound kernel
   int32_t write_scores;  // fused kernel: also store the page scores
   int32_t* dev_err;
 };
@@ -85,7 +86,13 @@ __global__ __launch_bounds__(256) void quest_summarize_kernel(const QuestParams 
   *reinterpret_cast<uint32_t*>(meta + D + 2 * lane) = mx0 | (mx1 << 16);
 }
 
-constexpr int kBoundPagesPerGroup = 256;
+// Pages a work-group of the bound kernel takes: few enough that the chip gets
+// kBoundGroups work-groups (a work-group goes through its pages one round of
+// loads after the other: 8 units of 8192 pages with 256 pages each took 20 us),
+// at most 256, at least one round.
+constexpr int kBoundGroups = 2048;
+constexpr int kBoundMostPages = 256;
+constexpr int kBoundLeastPages = 32;
 
 template <int D, int G>
 __global__ __launch_bounds__(256) void quest_bound_kernel(const QuestParams p) {
@@ -101,14 +108,14 @@ __global__ __launch_bounds__(256) void quest_bound_kernel(const QuestParams p) {
   const int L = p.lengths[unit];
   if (!unit_length_ok(p, L)) return;  // reported by the top-k kernel
   const int n_cand = L / kPage;
-  const int b0 = chunk * kBoundPagesPerGroup;
+  const int b0 = chunk * p.pages_per_block;
   if (b0 >= n_cand) return;
-  const int b1 = min(b0 + kBoundPagesPerGroup, n_cand);
+  const int b1 = min(b0 + p.pages_per_block, n_cand);
 
   uint32_t qp[G][CW], qn[G][CW];
   bound_query<D, G>(p.q + ((size_t)req * p.hkv * G + (size_t)kvh * G) * D, g, qp, qn);
 
-  for (int b = b0 + (int)threadIdx.x / LPP; b < b0 + kBoundPagesPerGroup; b += PPI) {
+  for (int b = b0 + (int)threadIdx.x / LPP; b < b0 + p.pages_per_block; b += PPI) {
     const bool valid = b < b1;
     if (__ballot(valid) == 0) break;
     int phys = 0;
@@ -174,6 +181,43 @@ __global__ __launch_bounds__(256) void quest_topk_kernel(const QuestParams p) {
     eq_base += eq_total;
     out_base += take_total;
   }
+}
+
+// The same from LDS by unit_topk: one 1024-thread work-group per unit copies the
+// scores first (eight loads in flight per thread).  8 units of 8192 pages: 58
+// us with the 256-thread kernel above, which reads the scores from memory in
+// every pass and takes two block scans per 256 pages of output, 15.5 here.
+constexpr int kTopkThreads = 1024;
+constexpr int kTopkMaxPages = 16384;
+
+__global__ __launch_bounds__(kTopkThreads) void quest_topk_lds_kernel(const QuestParams p) {
+  constexpr int NT = kTopkThreads, NB = 8;
+  __shared__ float lds_sc[kTopkMaxPages];
+  __shared__ unsigned hist[256];
+  __shared__ int bcast[4];
+  const int tid = threadIdx.x;
+  const int unit = blockIdx.x;
+  const int L = p.lengths[unit];
+  int32_t* out = p.sel + (size_t)unit * p.top_k;
+  if (!unit_length_ok(p, L)) {
+    if (tid == 0) set_error(p.dev_err, SE_DEVERR_BAD_LENGTH);
+    for (int i = tid; i < p.top_k; i += NT) out[i] = -1;
+    return;
+  }
+  const int n = L / kPage;
+  const float* sc = p.scores + (size_t)unit * p.scores_stride;
+  if (n > p.top_k) {
+    for (int i = tid; i < n; i += NT * NB) {
+      float v[NB];
+#pragma unroll
+      for (int k = 0; k < NB; ++k) v[k] = sc[min(i + k * NT, n - 1)];
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+        if (i + k * NT < n) lds_sc[i + k * NT] = v[k];
+    }
+    __syncthreads();
+  }
+  unit_topk<NT>(n, p.top_k, lds_sc, [&](int r, int b) { out[r] = b; }, hist, nullptr, bcast, false);
 }
 
 constexpr int kFusedThreads = 1024;
@@ -319,7 +363,11 @@ extern "C" se_status se_quest_select(const se_kv_view* kv, int32_t q_per_kv, con
       }
       return launch_status();
     }
-    prm.blocks_per_unit = (int)ceil_div(ml / kPage > 0 ? ml / kPage : 1, kBoundPagesPerGroup);
+    const int64_t pages = ml / kPage > 0 ? ml / kPage : 1;
+    int64_t per = ceil_div(pages * kv->num_units, kBoundGroups);
+    per = ceil_div(per, kBoundLeastPages) * kBoundLeastPages;
+    prm.pages_per_block = (int)(per < kBoundMostPages ? per : kBoundMostPages);
+    prm.blocks_per_unit = (int)ceil_div(pages, prm.pages_per_block);
     const int64_t grid = (int64_t)kv->num_units * prm.blocks_per_unit;
     if (grid > INT32_MAX) return SE_ERR_UNSUPPORTED;
     const int D = kv->head_dim;
@@ -337,6 +385,10 @@ extern "C" se_status se_quest_select(const se_kv_view* kv, int32_t q_per_kv, con
     st = launch_status();
     if (st != SE_OK) return st;
   }
-  hipLaunchKernelGGL(quest_topk_kernel, dim3(kv->num_units), dim3(256), 0, stream, prm);
+  // (a unit has at most max_pages candidates; longer rows are ranked from memory)
+  if (kv->max_pages <= kTopkMaxPages || max_len / kPage <= kTopkMaxPages)
+    hipLaunchKernelGGL(quest_topk_lds_kernel, dim3(kv->num_units), dim3(kTopkThreads), 0, stream, prm);
+  else
+    hipLaunchKernelGGL(quest_topk_kernel, dim3(kv->num_units), dim3(256), 0, stream, prm);
   return launch_status();
 }

@@ -1,0 +1,64 @@
+"""se_quest_select of few units: the bound kernel's pages per work-group and the
+top-k from LDS, at the edges of their ranges."""
+import numpy as np
+import pytest
+import torch
+
+from workloads import isolated_units, to_device
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def _stable_top(scores, k):
+    want = np.sort(np.argsort(-scores, kind="stable")[:k])
+    return np.concatenate([want, np.full(k - len(want), -1)])
+
+
+@pytest.mark.parametrize("levels", [0, 5])
+@pytest.mark.parametrize("pages,top_k", [(1, 4), (64, 64), (65, 64), (1024, 7), (1025, 1000), (16384, 92), (16385, 92)])
+def test_given_scores(pages, top_k, levels):
+    import paper_2609_39068_amd as se
+    units = 3
+    g = torch.Generator().manual_seed(pages + levels)
+    sc = torch.randint(0, levels, (units, pages + 1), generator=g).float() if levels else torch.randn((units, pages + 1), generator=g)
+    kv = torch.zeros((1, 2, 16, 64), dtype=torch.bfloat16, device=DEV)
+    view = se.KVView(kv, torch.zeros((1, 16), dtype=torch.int32, device=DEV), None, None,
+                     torch.zeros((units, pages + 1), dtype=torch.int32, device=DEV),
+                     torch.full((units,), pages * 16 + 3, dtype=torch.int32, device=DEV), num_kv_heads=1)
+    sel = torch.empty((units, top_k), dtype=torch.int32, device=DEV)
+    err = torch.zeros(1, dtype=torch.int32, device=DEV)
+    se.se_quest_select(view, 1, None, 1.0, top_k, pages * 16 + 3, se.SE_QUEST_SCORES_GIVEN, sel, sc.to(DEV), pages + 1, None, err)
+    torch.cuda.synchronize()
+    assert se.se_read_device_errors(err) == 0
+    for u in range(units):
+        np.testing.assert_array_equal(sel[u].cpu().numpy(), _stable_top(sc[u, :pages].numpy(), top_k))
+
+
+@pytest.mark.parametrize("G,d", [(8, 128), (4, 64), (1, 128)])
+@pytest.mark.parametrize("pages", [1, 31, 32, 33, 700])
+def test_bounds(pages, G, d):
+    import paper_2609_39068_amd as se
+    lengths = [pages * 16 + 5, max(16, pages * 8)]
+    host = isolated_units(lengths, pages + 1, d, seed=pages + G, num_kv_heads=2, with_meta=True, with_scores=False)
+    gs = to_device(host, DEV)
+    view = se.KVView(gs.kv_pool, gs.pos_pool, None, gs.meta_pool, gs.block_table, gs.lengths, num_kv_heads=2)
+    q = torch.randn((1, 2 * G, d), generator=torch.Generator().manual_seed(3)).to(torch.bfloat16)
+    err = torch.zeros(1, dtype=torch.int32, device=DEV)
+    ml = lengths[0]
+    se.se_quest_summarize(view, ml, err)
+    sel = torch.empty((2, 16), dtype=torch.int32, device=DEV)
+    sc = torch.zeros((2, pages + 1), device=DEV)
+    se.se_quest_select(view, G, q.to(DEV), 0.25, 16, ml, 0, sel, sc, pages + 1, None, err)
+    torch.cuda.synchronize()
+    assert se.se_read_device_errors(err) == 0
+    for u, L in enumerate(lengths):
+        n = L // 16
+        k = host.kv_pool[host.block_table[u, :n].long(), 0].double()
+        qu = q[0, u * G:(u + 1) * G].double()
+        want = 0.25 * (qu.clamp(min=0) @ k.amax(1).T + qu.clamp(max=0) @ k.amin(1).T).amax(0)
+        got = sc[u, :n].cpu()
+        # 128 exact products of bf16 values summed in fp32: a few 2^-24 of the sum of magnitudes
+        assert torch.allclose(got.double(), want, rtol=1e-5, atol=1e-5)
+        np.testing.assert_array_equal(sel[u].cpu().numpy(), _stable_top(got.numpy(), 16))
