@@ -21,16 +21,17 @@
 // contiguous run of slots, so two block scans (of the tied count and of the
 // selected count) give each thread its output offset.
 //
-// Slot attention: one 512-thread work-group per unit.  The selected slots are
-// translated once into kv-pool row indices in LDS (the appended token's row is
-// read from k_new / v_new instead, so no wavefront reads a row another one
-// wrote).  Each wavefront takes a contiguous share of the rows, eight rows per
-// pass: for QK, 8 lanes share a key row (D/8 columns each, 16-byte loads) and
-// reduce their bf16-pair dot products over the 8 lanes; the online softmax
-// keeps one maximum per head; the pass's weights are broadcast through LDS and
-// every lane accumulates its own D/64 value columns of the 8 rows (one
-// coalesced row per load instruction).  The next pass's key and value loads
-// are issued before the current pass is reduced.  Wavefronts combine in LDS.
+// Slot attention: one work-group per unit.  The selected slots are translated
+// once into kv-pool row indices in LDS (the appended token's row is read from
+// k_new / v_new instead, so no wavefront reads a row another one wrote).  Each
+// wavefront takes a contiguous share of the rows, sixteen rows per pass: QK on
+// the matrix cores (the rows as the B operand, the query heads repeated over
+// the A rows, so that every 16-lane group ends with every head's logits of
+// its 16 keys and takes one head of them), an online softmax with one reference
+// per head, raised only when a logit passes it by 2^8, the pass's weights
+// through LDS, and every lane accumulating its own D/64 value columns of the
+// rows (one coalesced row per load instruction).  Two register buffers keep
+// the next pass's loads in flight.  Wavefronts combine in LDS.
 #include "quest_core.h"
 
 namespace se {
@@ -562,53 +563,34 @@ struct GatherParams {
   int32_t* dev_err;
 };
 
-// Cross-lane steps of the gather pass, all in VALU (DPP and permlane swaps,
-// no LDS permutes).  row8_sum: the sum over each group of 8 lanes, in all 8
-// (quad sums, then each lane adds the mirror lane of its half-row, which
-// holds the other quad's sum: the pairs of an xor-1/2/4 butterfly, so the
-// same rounding).  lane8_max: the maximum over the 8 lanes of equal lane % 8
-// (bit 3 by a rotation of each 16-lane row by 8, bits 5 and 4 by permlane
-// swaps).
-constexpr int kRowHalfMirror = 0x141;  // DPP row_half_mirror: lane i of 8 reads lane 7 - i
-constexpr int kRowRor8 = 0x128;        // DPP row_ror:8: lane i of 16 reads lane (i + 8) % 16
-__device__ __forceinline__ float row8_sum(float v) {
+// Reductions over the 16 lanes of a DPP row, in all of them: within quads, the
+// other quad of the 8 (row_half_mirror), the other 8 (row_mirror).
+__device__ __forceinline__ float row16_max(float v) {
+  v = fmaxf(v, dpp_f<kQuadXor1>(v));
+  v = fmaxf(v, dpp_f<kQuadXor2>(v));
+  v = fmaxf(v, dpp_f<0x141>(v));
+  return fmaxf(v, dpp_f<0x140>(v));
+}
+__device__ __forceinline__ float gather_row16_sum(float v) {
   v = quad_sum(v);
-  return v + dpp_f<kRowHalfMirror>(v);
-}
-__device__ __forceinline__ float lane8_sum(float v) {
-  v += dpp_f<kRowRor8>(v);
-  const uint32_t b = __float_as_uint(v);
-  const auto h = __builtin_amdgcn_permlane32_swap(b, b, false, false);
-  const float y = __uint_as_float(h[0]) + __uint_as_float(h[1]);
-  const uint32_t c = __float_as_uint(y);
-  const auto r = __builtin_amdgcn_permlane16_swap(c, c, false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float lane8_max(float v) {
-  v = fmaxf(v, dpp_f<kRowRor8>(v));
-  const uint32_t b = __float_as_uint(v);
-  const auto h = __builtin_amdgcn_permlane32_swap(b, b, false, false);
-  const float y = fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
-  const uint32_t c = __float_as_uint(y);
-  const auto r = __builtin_amdgcn_permlane16_swap(c, c, false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  v += dpp_f<0x141>(v);
+  return v + dpp_f<0x140>(v);
 }
 
+typedef __bf16 gather_bf16x8 __attribute__((ext_vector_type(8)));
+typedef float gather_f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t gather_u32x4 __attribute__((ext_vector_type(4)));
 
-template <int D>
-struct GatherRow {
-  static constexpr int QW = D / 16;  // 32-bit words of a key row per lane (8 lanes per row)
-  static constexpr int VW = D / 64;  // value columns per lane
-};
+constexpr int kGatherRows = 16;  // rows per pass
 
 template <int D, int G, int NT>
 __global__ __launch_bounds__(NT, (G >= 4 ? 2 : 4) * kGatherThreads / NT) void gather_attend_kernel(const GatherParams p) {
   constexpr int kGatherWaves = NT / kWave;
-  constexpr int QW = GatherRow<D>::QW;
-  constexpr int VC = GatherRow<D>::VW;
+  constexpr int KS = D / 32;                 // contraction steps of a 16x16x32 MFMA
+  constexpr int VC = D / 64;                 // value columns per lane
+  constexpr int NT4 = G > 4 ? G / 4 : 1;     // A tiles: heads 4 * t + (row % 4) of a group of 8
   __shared__ uint32_t s_row[kGatherMaxSel];
-  __shared__ float s_w[kGatherWaves][8][G];
+  __shared__ __attribute__((aligned(16))) float s_w[kGatherWaves][kGatherRows][G];
   __shared__ float s_m[kGatherWaves][G], s_l[kGatherWaves][G];
   __shared__ float s_o[kGatherWaves][G][D];
   __shared__ int s_scan[kGatherWaves + 1];
@@ -654,23 +636,16 @@ __global__ __launch_bounds__(NT, (G >= 4 ? 2 : 4) * kGatherThreads / NT) void ga
   }
 
   // ---- queries (loaded first, so that their latency overlaps the row
-  // translation): lane (row r8 = lane/8, c8 = lane%8) holds columns [c8*D/8, ...)
-  // of the G rows
-  const int c8 = lane & 7;
-  const int r8 = lane >> 3;
-  uint32_t qr[G][QW];
-  {
-    const uint16_t* qb = p.q + ((size_t)req * Hq + (size_t)kvh * G) * D + c8 * (D / 8);
+  // translation) as A operands: lane l holds row l % 16, that is head
+  // (l % 16) % 4 (% G) of the tile, contraction indices 8 * (l / 16) .. + 7 of each step
+  const int grp = lane >> 4;
+  const int col = lane & 15;
+  uint4 qa[NT4][KS];
 #pragma unroll
-    for (int g = 0; g < G; ++g)
+  for (int t = 0; t < NT4; ++t) {
+    const uint16_t* qb = p.q + ((size_t)req * Hq + (size_t)kvh * G + 4 * t + (col & 3) % G) * D + grp * 8;
 #pragma unroll
-      for (int i = 0; i < QW; i += 4) {
-        const uint4 t = *reinterpret_cast<const uint4*>(qb + (size_t)g * D + 2 * i);
-        qr[g][i] = t.x;
-        qr[g][i + 1] = t.y;
-        qr[g][i + 2] = t.z;
-        qr[g][i + 3] = t.w;
-      }
+    for (int k = 0; k < KS; ++k) qa[t][k] = *reinterpret_cast<const uint4*>(qb + 32 * k);
   }
   // ---- the selected rows (entries < 0 skipped; at or past L reported and
   // skipped), 2 * NT entries a round: a thread's two entries (c0 + tid and
@@ -729,33 +704,26 @@ __global__ __launch_bounds__(NT, (G >= 4 ? 2 : 4) * kGatherThreads / NT) void ga
   const uint16_t* knew = append ? p.k_new + ((size_t)req * p.num_kv_heads + kvh) * D : nullptr;
   const uint16_t* vnew = append ? p.v_new + ((size_t)req * p.num_kv_heads + kvh) * D : nullptr;
 
-  // the wavefront's share of the rows, in passes of 8
+  // the wavefront's share of the rows, in passes of 16
   const int per = ceil_div_dev(n_sel, kGatherWaves);
   const int rb = min(n_sel, wv * per), re = min(n_sel, rb + per);
-  const int n_pass = ceil_div_dev(re - rb, 8);
+  const int n_pass = ceil_div_dev(re - rb, kGatherRows);
 
   struct Buf {
-    uint32_t k[QW];
-    uint32_t v[8];
+    gather_u32x4 k[KS];
+    uint32_t v[kGatherRows];
   };
+  // rows are read once: nontemporal loads (as the decode stream's); rows past
+  // the share re-read its last one
   auto load = [&](int ps, Buf& bf) {
-    const int e = min(rb + ps * 8 + r8, re - 1);
-    const uint32_t row = s_row[max(e, 0)];
-    const uint16_t* ksrc = row == kNewRow ? knew : p.kv + (size_t)row * D;
-    // rows are read once: nontemporal loads (as the decode stream's)
-    const gather_u32x4* k4 = reinterpret_cast<const gather_u32x4*>(ksrc + c8 * (D / 8));
+    const uint32_t row = s_row[max(min(rb + ps * kGatherRows + col, re - 1), 0)];
+    const gather_u32x4* k4 =
+        reinterpret_cast<const gather_u32x4*>((row == kNewRow ? knew : p.kv + (size_t)row * D) + grp * 8);
 #pragma unroll
-    for (int i = 0; i < QW; i += 4) {
-      const gather_u32x4 t = __builtin_nontemporal_load(k4 + i / 4);
-      bf.k[i] = t.x;
-      bf.k[i + 1] = t.y;
-      bf.k[i + 2] = t.z;
-      bf.k[i + 3] = t.w;
-    }
+    for (int i = 0; i < KS; ++i) bf.k[i] = __builtin_nontemporal_load(k4 + 4 * i);
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const int er = min(rb + ps * 8 + r, re - 1);
-      const uint32_t vr = __builtin_amdgcn_readfirstlane(s_row[max(er, 0)]);  // one row per wavefront
+    for (int r = 0; r < kGatherRows; ++r) {
+      const uint32_t vr = __builtin_amdgcn_readlane(row, r);  // one row per wavefront
       const uint16_t* vsrc = vr == kNewRow ? vnew : p.kv + ((size_t)vr + kPage) * D;
       if (VC == 2)
         bf.v[r] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(vsrc) + lane);
@@ -764,42 +732,59 @@ __global__ __launch_bounds__(NT, (G >= 4 ? 2 : 4) * kGatherThreads / NT) void ga
     }
   };
 
-  float m[G], l[G], acc[G][VC];
+  // per head the weighted value columns; per lane the reference and the
+  // denominator's share of its own heads, grp and grp + 4 (lanes of groups at or past G own none)
+  constexpr float kBump = 8.0f;
+  const bool owns = grp < G;
+  float m[NT4], l[NT4], acc[G][VC];
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    m[g] = -INFINITY;
-    l[g] = 0.f;
+  for (int t = 0; t < NT4; ++t) {
+    m[t] = -INFINITY;
+    l[t] = 0.f;
+  }
+#pragma unroll
+  for (int g = 0; g < G; ++g)
 #pragma unroll
     for (int c = 0; c < VC; ++c) acc[g][c] = 0.f;
-  }
-  // one pass: logits of row r8 for every head (reduced over the row's 8
-  // lanes), the pass maximum per head, rescale, weights through LDS, values
   auto pass = [&](int ps, const Buf& cur) {
-    float z[G];
+    float z[NT4];
+    bool need = false;
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      float a = 0.f;
+    for (int t = 0; t < NT4; ++t) {
+      gather_f32x4 a = gather_f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int i = 0; i < QW; ++i) a = dot2bf16(qr[g][i], cur.k[i], a);
-      a = row8_sum(a);
-      z[g] = rb + ps * 8 + r8 < re ? a * p.scale_log2 : -INFINITY;
+      for (int k = 0; k < KS; ++k)
+        a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(gather_bf16x8, qa[t][k]),
+                                                    __builtin_bit_cast(gather_bf16x8, cur.k[k]), a, 0, 0, 0);
+      // a[r]: head r of the tile (r % G) against key col, the same in every group; this group's is a[grp]
+      const float own = grp == 0 ? a[0] : grp == 1 ? a[1] : grp == 2 ? a[2] : a[3];
+      z[t] = owns && rb + ps * kGatherRows + col < re ? own * p.scale_log2 : -INFINITY;
+      need = need || z[t] > m[t] + kBump;
+    }
+    if (__ballot(need) != 0) {
+#pragma unroll
+      for (int t = 0; t < NT4; ++t) {
+        const float mn = fmaxf(m[t], row16_max(z[t]));
+        const float f = m[t] == -INFINITY ? 0.f : fast_exp2(m[t] - mn);
+        l[t] *= f;
+        m[t] = mn;
+#pragma unroll
+        for (int h = 0; h < (G < 4 ? G : 4); ++h) {
+          const float fh = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f), 16 * h));
+#pragma unroll
+          for (int c = 0; c < VC; ++c) acc[4 * t + h][c] *= fh;
+        }
+      }
     }
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      float mx = z[g];
-      mx = lane8_max(mx);
-      const float mn = fmaxf(m[g], mx);
-      const float corr = fast_exp2(m[g] - mn);  // m = -inf at first: 0
-      m[g] = mn;
-      const float w = fast_exp2(z[g] - mn);
-      if (c8 == 0) s_w[wv][r8][g] = w;
-      l[g] = fmaf(l[g], corr, w);  // row r8's share (the row's 8 lanes hold the same)
-#pragma unroll
-      for (int c = 0; c < VC; ++c) acc[g][c] *= corr;
+    for (int t = 0; t < NT4; ++t) {
+      const float w = z[t] == -INFINITY ? 0.f : fast_exp2(z[t] - m[t]);
+      l[t] += w;
+      if (owns) s_w[wv][col][grp + 4 * t] = w;
     }
     wave_lds_sync();
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
+    for (int r = 0; r < kGatherRows; ++r) {
       float vf[VC];
       if (VC == 2) {
         vf[0] = bf16lo(cur.v[r]);
@@ -816,38 +801,35 @@ __global__ __launch_bounds__(NT, (G >= 4 ? 2 : 4) * kGatherThreads / NT) void ga
     }
     wave_lds_sync();
   };
-  // three buffers, two passes in flight while one is reduced; loads past the
-  // share re-read its last row, so every step issues the same loads and the
-  // waits stay partial (the loop is unrolled by three: every buffer keeps its
-  // registers)
+  // two buffers: one pass in flight while the other is reduced; every step
+  // issues the same loads, so the waits stay partial
   if (n_pass > 0) {
-    Buf b0, b1, b2;
+    Buf b0, b1;
     load(0, b0);
     load(1, b1);
-    load(2, b2);
-    for (int ps = 0; ps < n_pass; ps += 3) {
+    for (int ps = 0; ps < n_pass; ps += 2) {
       pass(ps, b0);
-      load(ps + 3, b0);
+      load(ps + 2, b0);
       if (ps + 1 < n_pass) pass(ps + 1, b1);
-      load(ps + 4, b1);
-      if (ps + 2 < n_pass) pass(ps + 2, b2);
-      load(ps + 5, b2);
+      load(ps + 3, b1);
     }
   }
-  // ---- combine the wavefronts (l: the sum of the 8 row lanes' shares)
+  // ---- combine the wavefronts (l: the sum over the 16 keys' lanes)
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    l[g] = lane8_sum(l[g]);
-    if (lane == 0) {
-      s_m[wv][g] = m[g];
-      s_l[wv][g] = l[g];
+  for (int t = 0; t < NT4; ++t) {
+    const float lt = gather_row16_sum(l[t]);
+    if (col == 0 && owns) {
+      s_m[wv][grp + 4 * t] = m[t];
+      s_l[wv][grp + 4 * t] = lt;
     }
+  }
+#pragma unroll
+  for (int g = 0; g < G; ++g)
 #pragma unroll
     for (int c = 0; c < VC; ++c) s_o[wv][g][lane * VC + c] = acc[g][c];
-  }
   __syncthreads();
   for (int i = tid; i < G * D; i += NT) {
-    const int g = i / D, col = i % D;
+    const int g = i / D, oc = i % D;
     float M = -INFINITY;
 #pragma unroll
     for (int w = 0; w < kGatherWaves; ++w) M = fmaxf(M, s_m[w][g]);
@@ -857,11 +839,11 @@ __global__ __launch_bounds__(NT, (G >= 4 ? 2 : 4) * kGatherThreads / NT) void ga
       for (int w = 0; w < kGatherWaves; ++w) {
         const float f = s_m[w][g] == -INFINITY ? 0.f : fast_exp2(s_m[w][g] - M);
         lsum += s_l[w][g] * f;
-        o += s_o[w][g][col] * f;
+        o += s_o[w][g][oc] * f;
       }
     }
-    o_out[(size_t)g * D + col] = lsum > 0.f ? o / lsum : 0.f;
-    if (col == 0 && p.lse != nullptr)
+    o_out[(size_t)g * D + oc] = lsum > 0.f ? o / lsum : 0.f;
+    if (oc == 0 && p.lse != nullptr)
       p.lse[(size_t)req * Hq + kvh * G + g] = lsum > 0.f ? (M + __log2f(lsum)) * kLn2 : -INFINITY;
   }
 }
