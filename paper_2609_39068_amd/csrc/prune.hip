@@ -4,7 +4,7 @@
 // positions [lo, hi) of a unit and I the positions of T a policy keeps, the
 // unit's resident set becomes (R minus T) union I; positions are not renumbered.
 //
-// One 256-thread work-group per unit:
+// One work-group per unit:
 //   1. The unit's block-table row goes to LDS (entries checked); one pass over
 //      the positions counts the interval's resident slots and finds the first
 //      and last of them.
@@ -22,7 +22,8 @@
 //      be a source of the same round -- and the pieces, positions and scores
 //      are stored at their ranks.  A destination is never above its source and
 //      later rounds read only slots above this round, so the next round's loads
-//      never meet this round's stores.
+//      never meet this round's stores and are issued before them: two rounds are
+//      in flight.
 //   4. The pages past the new length are reported, the length written, and the
 //      Quest summaries (when the view has them) of the pages from the
 //      interval's first slot on are rebuilt from the stored keys.
@@ -32,9 +33,15 @@
 
 namespace se {
 
-constexpr int kPruneThreads = 256;
+// Threads per unit: with at most one work-group per compute unit 1024, which keep
+// twice the rows in flight there (32 units: 388 us against 439 with 512 threads,
+// 659 with 256 and no second round in flight; 256 units: 854, 859, 904),
+// otherwise 512 (2048 units: 6.42 ms against 6.49 with 1024, at the rate of a plain
+// copy).
+constexpr int kPruneThreads = 512;
+constexpr int kPruneThreadsWide = 1024;
+constexpr int kPruneWideUnits = 256;
 constexpr int kPruneMaxPages = 8192;   // 131072 slots per unit
-constexpr int kPruneRound = kWave;     // slots per compaction round
 constexpr int kPruneBatch = 8;         // positions in flight per thread in the scans
 
 struct PruneParams {
@@ -64,14 +71,14 @@ __device__ __forceinline__ uint64_t prune_key(float score, int32_t pos) {
   return ((uint64_t)float_key(score) << 32) | (uint64_t)(~((uint32_t)pos ^ 0x80000000u));
 }
 
-template <int D>
-__global__ __launch_bounds__(kPruneThreads, 4) void prune_interval_kernel(const PruneParams p) {
-  constexpr int NT = kPruneThreads;
+template <int D, int NT>
+__global__ __launch_bounds__(NT, 4) void prune_interval_kernel(const PruneParams p) {
+  constexpr int ROUND = kWave;               // slots per compaction round
   constexpr int PPS = 4 * D / 16;            // 16-byte pieces of a slot's key and value rows
   constexpr int KP = D / 8;                  // of them in the key row
   constexpr int SPK = NT / PPS;              // slots covered by one piece per thread
-  constexpr int KPT = kPruneRound / SPK;     // pieces per thread per round
-  static_assert(KPT * SPK == kPruneRound, "whole slots per round");
+  constexpr int KPT = ROUND / SPK;           // pieces per thread per round
+  static_assert(KPT * SPK == ROUND && NT >= 256, "whole slots per round; threads 0..255 own one bin each");
   __shared__ int s_bt[kPruneMaxPages];
   __shared__ unsigned s_hist[256];
   __shared__ int s_scan[NT / kWave + 1];
@@ -148,7 +155,7 @@ __global__ __launch_bounds__(kPruneThreads, 4) void prune_interval_kernel(const 
     uint64_t prefix = 0, mask = 0;
     int k = budget;
     for (int shift = 56; shift >= 0; shift -= 8) {
-      s_hist[tid] = 0;  // NT == 256 bins
+      if (tid < 256) s_hist[tid] = 0;
       __syncthreads();
       for (int b = first + tid; b <= last; b += NT * kPruneBatch) {
         int32_t ps[kPruneBatch];
@@ -173,7 +180,7 @@ __global__ __launch_bounds__(kPruneThreads, 4) void prune_interval_kernel(const 
         }
       }
       __syncthreads();
-      const int v = (int)s_hist[255 - tid];  // thread t counts digit 255 - t
+      const int v = tid < 256 ? (int)s_hist[255 - tid] : 0;  // thread t counts digit 255 - t
       int total;
       const int excl = block_exclusive_scan<NT>(v, s_scan, &total);
       if (v > 0 && excl < k && excl + v >= k) {
@@ -196,18 +203,28 @@ __global__ __launch_bounds__(kPruneThreads, 4) void prune_interval_kernel(const 
 
   // ---- 3. order-keeping compaction from the round holding the first interval slot
   const uint8_t* kmrow = by_mask ? p.keep_mask + (size_t)unit * p.mask_stride : nullptr;
-  const int r0 = first & ~(kPruneRound - 1);
+  const int r0 = first & ~(ROUND - 1);
   int base = r0;  // slots kept below the round: every slot below `first` stays in place
   // A lane's keep flag needs its slot's position, then the mask byte at that
   // position (or the slot's score): both are fetched ahead -- the position two
-  // rounds ahead, the second input one round ahead -- so that a round waits
-  // only for its own rows.  Those slots are above every destination written
-  // before their round, so the values read are the ones the round decides on.
-  auto load_pos = [&](int s) -> int32_t { return s < L ? p.pos_pool[slot_addr(s)] : INT_MIN; };
-  auto load_aux = [&](int s, int32_t ps) -> float {
-    if (s >= L || !in_t(ps)) return 0.f;
-    if (by_mask) return (float)kmrow[(int64_t)ps - lo];
-    return keep_none ? 0.f : p.score_pool[slot_addr(s)];
+  // rounds ahead, the second input one round ahead.  Those slots are above every
+  // destination written before their round, so the values read are the ones the
+  // round decides on.
+  struct Flags {
+    int32_t pos;
+    float aux;
+  };
+  auto load_pos = [&](int c0, Flags& f) {
+    const int s = c0 + lane;
+    f.pos = s < L ? p.pos_pool[slot_addr(s)] : INT_MIN;
+  };
+  auto load_aux = [&](int c0, Flags& f) {
+    const int s = c0 + lane;
+    f.aux = 0.f;
+    if (s < L && in_t(f.pos)) {
+      if (by_mask) f.aux = (float)kmrow[(int64_t)f.pos - lo];
+      else if (!keep_none) f.aux = p.score_pool[slot_addr(s)];
+    }
   };
   auto keep_of = [&](int s, int32_t ps, float aux) -> bool {
     if (s >= L) return false;
@@ -215,63 +232,91 @@ __global__ __launch_bounds__(kPruneThreads, 4) void prune_interval_kernel(const 
     if (by_mask) return aux != 0.f;
     return !keep_none && (prune_key(aux, ps) & kmask) >= kprefix;
   };
-  int32_t pos0 = load_pos(r0 + lane);
-  float aux0 = load_aux(r0 + lane, pos0);
-  int32_t pos1 = load_pos(r0 + kPruneRound + lane);
-  for (int c0 = r0; c0 < L; c0 += kPruneRound) {
-    const bool keep = keep_of(c0 + lane, pos0, aux0);
-    const float aux1 = load_aux(c0 + kPruneRound + lane, pos1);
-    const int32_t pos2 = load_pos(c0 + 2 * kPruneRound + lane);
-    const uint64_t bits = __builtin_amdgcn_ballot_w64(keep);  // the same in every wavefront
-    const int n_keep = __popcll(bits);
-    pos0 = pos1;
-    aux0 = aux1;
-    pos1 = pos2;
-    if (bits == (n_keep == 64 ? ~0ull : ((1ull << n_keep) - 1)) && base == c0) {
-      base += n_keep;  // the round's kept slots are its first ones and already in place
-      continue;
-    }
+  // One round's moving pieces in registers.
+  struct Batch {
     u32x4_t buf[KPT];
     int dst[KPT];
     int32_t mpos[KPT];
     float mscore[KPT];
-    const int pc = tid % PPS;
+    bool any;  // the same in every thread
+  };
+  const int pc = tid % PPS;
+  // read whether there are scores or not (they are stored only if so)
+  const float* scores = p.score_pool != nullptr ? p.score_pool : reinterpret_cast<const float*>(p.pos_pool);
+  // The round at c0: its keep flags (the same ballot in every wavefront), and the loads of its moving rows.
+  auto load_round = [&](int c0, const Flags& f, Batch& m) {
+    const uint64_t bits = __builtin_amdgcn_ballot_w64(keep_of(c0 + lane, f.pos, f.aux));
+    const int n_keep = __popcll(bits);
+    // the round's kept slots are its first ones and already in place
+    const bool in_place = base == c0 && bits == (n_keep == 64 ? ~0ull : ((1ull << n_keep) - 1));
+    m.any = !in_place;
+    if (in_place) {
+      base += n_keep;
+      return;
+    }
 #pragma unroll
     for (int k = 0; k < KPT; ++k) {
       const int j = tid / PPS + SPK * k;
       const int s = c0 + j;
       const bool kept = (bits >> j) & 1ull;
       const int d = base + __popcll(bits & ((1ull << j) - 1ull));
-      dst[k] = (kept && d != s) ? d : -1;
-      buf[k] = u32x4_t{0u, 0u, 0u, 0u};
-      mpos[k] = 0;
-      mscore[k] = 0.f;
-      if (dst[k] >= 0) {
-        const uint16_t* pg = p.kv + (size_t)s_bt[s >> 4] * 2 * kPage * D;
-        const int row = s & (kPage - 1);
-        const uint16_t* src = pc < KP ? pg + row * D + pc * 8 : pg + kPage * D + row * D + (pc - KP) * 8;
-        buf[k] = *reinterpret_cast<const u32x4_t*>(src);
-        if (pc == 0) mpos[k] = p.pos_pool[slot_addr(s)];
-        if (pc == 1 && p.score_pool != nullptr) mscore[k] = p.score_pool[slot_addr(s)];
-      }
+      m.dst[k] = (kept && d != s) ? d : -1;
+      // unconditional loads, so that waiting for this round's leaves the next round's in
+      // flight: a piece that does not move reads the round's first line instead
+      const bool mv = m.dst[k] >= 0;
+      const int sm = mv ? s : c0;
+      const int row = sm & (kPage - 1);
+      const uint16_t* pg = p.kv + (size_t)s_bt[sm >> 4] * 2 * kPage * D;
+      const uint16_t* src = pc < KP ? pg + row * D + pc * 8 : pg + kPage * D + row * D + (pc - KP) * 8;
+      m.buf[k] = *reinterpret_cast<const u32x4_t*>(mv ? src : pg);
+      m.mpos[k] = p.pos_pool[slot_addr(sm)];
+      m.mscore[k] = scores[slot_addr(sm)];
     }
-    // every load of the round has returned before any store of it
+    base += n_keep;
+  };
+  auto store_round = [&](const Batch& m) {
+    // every load of the round has returned, in every wavefront, before any store of it
 #pragma unroll
     for (int k = 0; k < KPT; ++k)
-      asm volatile("" ::"v"(buf[k].x), "v"(buf[k].y), "v"(buf[k].z), "v"(buf[k].w), "v"(mpos[k]), "v"(mscore[k]));
-    __syncthreads();
+      asm volatile("" ::"v"(m.buf[k].x), "v"(m.buf[k].y), "v"(m.buf[k].z), "v"(m.buf[k].w), "v"(m.mpos[k]), "v"(m.mscore[k]));
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 #pragma unroll
     for (int k = 0; k < KPT; ++k) {
-      const int d = dst[k];
+      const int d = m.dst[k];
       if (d < 0) continue;
       uint16_t* pg = p.kv + (size_t)s_bt[d >> 4] * 2 * kPage * D;
       const int row = d & (kPage - 1);
       uint16_t* out = pc < KP ? pg + row * D + pc * 8 : pg + kPage * D + row * D + (pc - KP) * 8;
-      *reinterpret_cast<u32x4_t*>(out) = buf[k];
-      if (pc == 0) p.pos_pool[slot_addr(d)] = mpos[k];
-      if (pc == 1 && p.score_pool != nullptr) p.score_pool[slot_addr(d)] = mscore[k];
+      *reinterpret_cast<u32x4_t*>(out) = m.buf[k];
+      if (pc == 0) p.pos_pool[slot_addr(d)] = m.mpos[k];
+      if (pc == 1 && p.score_pool != nullptr) p.score_pool[slot_addr(d)] = m.mscore[k];
     }
-    base += n_keep;
+  };
+  // The next round's rows are loaded before this round's are stored: they lie
+  // above every destination of this round.
+  Flags fl0, fl1;
+  load_pos(r0, fl0);
+  load_aux(r0, fl0);
+  load_pos(r0 + ROUND, fl1);
+  Batch ma, mb;
+  auto advance = [&](int c0, Batch& m) {  // loads round c0
+    load_aux(c0 + ROUND, fl1);
+    Flags fl2;
+    load_pos(c0 + 2 * ROUND, fl2);
+    load_round(c0, fl0, m);
+    fl0 = fl1;
+    fl1 = fl2;
+  };
+  ma.any = mb.any = false;
+  if (r0 < L) advance(r0, ma);
+  for (int c0 = r0; c0 < L; c0 += 2 * ROUND) {
+    mb.any = false;
+    if (c0 + ROUND < L) advance(c0 + ROUND, mb);
+    if (ma.any) store_round(ma);
+    ma.any = false;
+    if (c0 + 2 * ROUND < L) advance(c0 + 2 * ROUND, ma);
+    if (mb.any) store_round(mb);
   }
   const int Lp = base;
 
@@ -344,9 +389,14 @@ extern "C" se_status se_prune_interval(const se_kv_view* kv, const int32_t* inte
   prm.freed_stride = freed_stride;
   prm.freed_count = freed_count;
   prm.dev_err = dev_err;
-  if (kv->head_dim == 128)
-    hipLaunchKernelGGL((prune_interval_kernel<128>), dim3(kv->num_units), dim3(kPruneThreads), 0, stream, prm);
-  else
-    hipLaunchKernelGGL((prune_interval_kernel<64>), dim3(kv->num_units), dim3(kPruneThreads), 0, stream, prm);
+  const bool wide = kv->num_units <= kPruneWideUnits;
+  const dim3 grid(kv->num_units), block(wide ? kPruneThreadsWide : kPruneThreads);
+  if (kv->head_dim == 128) {
+    if (wide) hipLaunchKernelGGL((prune_interval_kernel<128, kPruneThreadsWide>), grid, block, 0, stream, prm);
+    else hipLaunchKernelGGL((prune_interval_kernel<128, kPruneThreads>), grid, block, 0, stream, prm);
+  } else {
+    if (wide) hipLaunchKernelGGL((prune_interval_kernel<64, kPruneThreadsWide>), grid, block, 0, stream, prm);
+    else hipLaunchKernelGGL((prune_interval_kernel<64, kPruneThreads>), grid, block, 0, stream, prm);
+  }
   return launch_status();
 }
