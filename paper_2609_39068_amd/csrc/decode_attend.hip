@@ -1589,7 +1589,12 @@ static_assert(wave_rows_pages<kAttendThreads, 4>() == (4 * 4 * kSteadyRows * 100
                   wave_rows_pages<kAttendThreadsWide, 4>() == (4 * 4 * kSteadyRows * 100 - 50) / RankWeights<4>::w[0],
               "per-wavefront steady eviction bounds");
 
-// Launches with at most one work-group per compute unit take 1024 threads.
+// Launches with at most one work-group per compute unit take 1024 threads, but
+// for units of a few pages (without a selection): the barriers of sixteen
+// wavefronts, most without a page, then cost more than the pages (H2O step of 8
+// units of 9 pages 13.7 us with 1024 threads, 11.3 with 512; 33 pages 17.1 and
+// 15.1; 240 units of 33 pages 22.4 and 19.6; 64 pages 20.4 either way).
+constexpr int kNarrowPages = 48;
 inline bool attend_wide(int num_units, int n_visit) {
   return (int64_t)num_units * ceil_div(n_visit, kMaxGroupPages) <= 256;
 }
@@ -1691,7 +1696,7 @@ static se_status attend_launch(const se_kv_view* kv, int32_t q_per_kv, const voi
 
   const int D = kv->head_dim;
   const int n_visit = attend_n_visit(max_len, kv->max_pages, top_k);
-  const bool wide = attend_wide(kv->num_units, n_visit);
+  const bool wide = attend_wide(kv->num_units, n_visit) && (sel_pages != nullptr || n_visit > kNarrowPages);
   const SplitShape s = split_shape(kv->num_units, n_visit, wide ? 256 : 512);
   const AttendWs lay = attend_ws_layout(kv->num_units, s, q_per_kv, D);
   if (ws == nullptr || ws_bytes < lay.total) return SE_ERR_WORKSPACE;
