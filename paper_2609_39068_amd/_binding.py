@@ -97,6 +97,7 @@ def _load():
         "se_read_device_errors": (I32, [P, P, P]),
         "se_status_string": (ctypes.c_char_p, [I32]),
         "se_version": (I32, []),
+        "se_observe_attend": (I32, [V, I32, P, P, P, P, F32, I32, P, P, P, I32, P, SZ, P, P]),
         "se_probe_read_pages": (I32, [P, ctypes.c_int64, P, ctypes.c_int64, I32, I32, P, P]),
     }
     for name, (res, args) in sig.items():
@@ -202,6 +203,29 @@ def se_decode_attend(view: KVView, q_per_kv, q, k_new, v_new, new_pos, sel_pages
         _ptr(logits, torch.float32, "logits"), int(logits_stride), _ptr(ws, None, "ws"),
         0 if ws is None else ws.numel() * ws.element_size(), _ptr(dev_err, torch.int32, "dev_err"),
         _stream(stream))
+    _check("se_decode_attend", st)
+
+
+def _observe_attend(view: KVView, q_per_kv, q, k_new, v_new, new_pos, scale, max_len, out, lse, group_max, stride, ws,
+                    dev_err, stream=None):
+    """se_decode_attend over every slot, with the maximum over each unit's query heads of the
+    logits ([num_units][stride]) in place of the logits; for OmniKVDecoder."""
+    s = view.struct
+    nreq = s.num_units // s.num_kv_heads
+    hq = s.num_kv_heads * q_per_kv
+    _need(q, nreq * hq * s.head_dim, "q")
+    _need(out, nreq * hq * s.head_dim, "out")
+    _need(lse, nreq * hq, "lse")
+    _need(k_new, s.num_units * s.head_dim, "k_new")
+    _need(v_new, s.num_units * s.head_dim, "v_new")
+    _need(new_pos, nreq, "new_pos")
+    _need(group_max, s.num_units * int(stride), "group_max")
+    st = _lib.se_observe_attend(
+        view.ref(), q_per_kv, _ptr(q, torch.bfloat16, "q"), _ptr(k_new, torch.bfloat16, "k_new"),
+        _ptr(v_new, torch.bfloat16, "v_new"), _ptr(new_pos, torch.int32, "new_pos"), float(scale), int(max_len),
+        _ptr(out, torch.float32, "out"), _ptr(lse, torch.float32, "lse"), _ptr(group_max, torch.float32, "group_max"),
+        int(stride), _ptr(ws, None, "ws"), 0 if ws is None else ws.numel() * ws.element_size(),
+        _ptr(dev_err, torch.int32, "dev_err"), _stream(stream))
     _check("se_decode_attend", st)
 
 

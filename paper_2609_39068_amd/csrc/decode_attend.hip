@@ -71,6 +71,7 @@ struct AttendParams {
   float* logits;
   int32_t logits_stride;
   int32_t logits_vec;  // logits rows 16-byte aligned
+  int32_t logits_max;  // one row per unit: the maximum over the group's heads
   float* part;
   float* pbuf;
   float* mref;
@@ -772,7 +773,7 @@ __device__ __forceinline__ void qk_page(const Lanes<D>& ln, const uint4 (&kb)[2 
 // Reference update, weight of the lane's pair, its workspace copy, and the
 // weights' broadcast through LDS (the page's PV follows).
 // lds_z (kLogits only): the page's logits for store_logits.
-template <int D, int G, bool kLogits, typename W>
+template <int D, int G, int kLogits, typename W>
 __device__ __forceinline__ void softmax_page(const AttendParams& p, const Lanes<D>& ln,
                                              const PageRef& pr, const float (&z)[kPairs<G>], WaveSoftmax<G>& ws,
                                              float* lds_pw, int lane, size_t ubase_p,
@@ -785,8 +786,18 @@ __device__ __forceinline__ void softmax_page(const AttendParams& p, const Lanes<
 #pragma unroll
   for (int k = 0; k < NP; ++k) {
     z2[k] = valid ? z[k] * p.scale_log2 : -INFINITY;
-    if (kLogits && valid) lds_z[(ln.own_head + 4 * k) * kPage + ln.own_row] = z[k] * p.scale;
+    if (kLogits == 1 && valid) lds_z[(ln.own_head + 4 * k) * kPage + ln.own_row] = z[k] * p.scale;
     need = need || (valid && (z2[k] > ws.m_own[k] + kBump));
+  }
+  if (kLogits == 2) {
+    // the row's largest logit over the group: the four lanes of a quad hold its heads (all of
+    // them, or, for groups of 1 and 2, copies), for groups of 8 two each
+    float mx = z[0];
+#pragma unroll
+    for (int k = 1; k < NP; ++k) mx = fmaxf(mx, z[k]);
+    mx = fmaxf(mx, dpp_f<kQuadXor1>(mx));
+    mx = fmaxf(mx, dpp_f<kQuadXor2>(mx));
+    if (valid && ln.own_head == 0) lds_z[ln.own_row] = mx * p.scale;
   }
   if (__ballot(need) != 0) {
 #pragma unroll
@@ -837,7 +848,7 @@ __device__ __forceinline__ void softmax_page(const AttendParams& p, const Lanes<
 template <int NT, int G>
 constexpr int kLogitsBurst = []() constexpr {
   int n = 16;
-  while (n * (NT / kWave) * G * kPage > kWeightCap) n /= 2;
+  while (n * (NT / kWave) * G * kPage > kWeightCap) n /= 2;  // (G rows a page: all heads)
   return n;
 }();
 
@@ -847,17 +858,17 @@ constexpr int kLogitsBurst = []() constexpr {
 // take their pages in groups of four here.  Stored page by page, 64 bytes per
 // head, the 134 MB of logits of 256 units of 32768 slots cost 250 us on top of
 // 662 us of attention.
-template <int G, typename Entry>
+template <int LR, typename Entry>
 __device__ __forceinline__ void store_logits(const AttendParams& p, const float* lds_z, const int* lds_lp, int i0, int n,
                                              int unit, int Lp, int lane, Entry entry) {
-  float* const base = p.logits + (size_t)unit * G * p.logits_stride;  // the unit's rows
-  for (int x = lane; x < G * 4 * ((n + 3) & ~3); x += kWave) {
+  float* const base = p.logits + (size_t)unit * LR * p.logits_stride;  // the unit's rows
+  for (int x = lane; x < LR * 4 * ((n + 3) & ~3); x += kWave) {
     // piece x: its group of four pages, then head, page of the group, four rows
-    const int q = x / (16 * G), y = x - q * (16 * G);
+    const int q = x / (16 * LR), y = x - q * (16 * LR);
     const int h = y >> 4, k = 4 * q + ((y >> 2) & 3), r = (y & 3) * 4;
     if (k < n) {
       const int s = lds_lp[entry(i0 + k)] * kPage + r;
-      const float4 v = *reinterpret_cast<const float4*>(lds_z + (k * G + h) * kPage + r);
+      const float4 v = *reinterpret_cast<const float4*>(lds_z + (k * LR + h) * kPage + r);
       float* dst = base + ((size_t)h * p.logits_stride + s);
       if (p.logits_vec && s + 4 <= Lp) {
         *reinterpret_cast<float4*>(dst) = v;
@@ -971,8 +982,8 @@ __device__ __forceinline__ const int* fused_quest_select(const AttendParams& p, 
 // slots (finish_steady_strided).  Two instantiations, chosen on the host from
 // the step's length bound, since carrying both paths costs the shorter one
 // registers.
-// kLogits: every slot's logits are an output.
-template <int D, int G, int NT, bool kWaveRows, bool kQuest, bool kLogits>
+// kLogits: 1: every slot's logits are an output; 2: their maximum over the group.
+template <int D, int G, int NT, bool kWaveRows, bool kQuest, int kLogits>
 __global__ __launch_bounds__(NT, 4) void decode_attend_kernel(const AttendParams p) {
   constexpr int NW = NT / kWave;  // wavefronts per work-group
   using LN = Lanes<D>;
@@ -1246,8 +1257,9 @@ __global__ __launch_bounds__(NT, 4) void decode_attend_kernel(const AttendParams
     __builtin_amdgcn_sched_barrier(0);
     load_v<D>(p, ln, cur, vb);
     // with kLogits, bursts of pages whose logits are stored together
-    constexpr int BURST = kLogits ? kLogitsBurst<NT, G> : 1;
-    float* const lds_z = lds_w + wave * (BURST * G * kPage);
+    constexpr int LR = kLogits == 2 ? 1 : G;  // rows of logits per unit
+    constexpr int BURST = kLogits ? kLogitsBurst<NT, LR> : 1;
+    float* const lds_z = lds_w + wave * (BURST * LR * kPage);
     for (int ib = 0; ib < n_my; ib += BURST) {
     const int ie = kLogits ? min(n_my, ib + BURST) : n_my;
     for (int i = kLogits ? ib : 0; i < ie; i += 2) {
@@ -1257,7 +1269,7 @@ __global__ __launch_bounds__(NT, 4) void decode_attend_kernel(const AttendParams
         qk_page<D, G>(ln, kbA, lds_q, z);
         load_k<D>(p, ln, nx2, kbA);
         softmax_page<D, G, kLogits, W>(p, ln, cur, z, ws, lds_p[wave], lane, ubase_p, lds_wh, lds_mr, wcap,
-                                       lds_z + (i - ib) * (G * kPage));
+                                       lds_z + (i - ib) * (LR * kPage));
         pv_page<D, G>(ln, vb, cur.nrows, ws, lds_p[wave]);
         load_v<D>(p, ln, nx1, vb);
         cur = nx1;
@@ -1270,15 +1282,15 @@ __global__ __launch_bounds__(NT, 4) void decode_attend_kernel(const AttendParams
         qk_page<D, G>(ln, kbB, lds_q, z);
         load_k<D>(p, ln, nx2, kbB);
         softmax_page<D, G, kLogits, W>(p, ln, cur, z, ws, lds_p[wave], lane, ubase_p, lds_wh, lds_mr, wcap,
-                                       lds_z + (i + 1 - ib) * (G * kPage));
+                                       lds_z + (i + 1 - ib) * (LR * kPage));
         pv_page<D, G>(ln, vb, cur.nrows, ws, lds_p[wave]);
         load_v<D>(p, ln, nx1, vb);
         cur = nx1;
         nx1 = nx2;
       }
     }
-    if constexpr (!kLogits) break;
-    store_logits<G>(p, lds_z, lds_lp, ib, ie - ib, unit, Lp, lane, entry);
+    if constexpr (kLogits == 0) break;
+    store_logits<LR>(p, lds_z, lds_lp, ib, ie - ib, unit, Lp, lane, entry);
     }
   }
 
@@ -1602,13 +1614,15 @@ inline bool attend_wide(int num_units, int n_visit) {
 template <int D, int G, int NT>
 static void launch_attend_nt(const AttendParams& prm, int grid, hipStream_t stream) {
   if (prm.sel != nullptr)  // Quest: no eviction code, per-wavefront rows are not used
-    hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, false, true, false>), dim3(grid), dim3(NT), 0, stream, prm);
+    hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, false, true, 0>), dim3(grid), dim3(NT), 0, stream, prm);
+  else if (prm.logits != nullptr && prm.logits_max)
+    hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, false, false, 2>), dim3(grid), dim3(NT), 0, stream, prm);
   else if (prm.logits != nullptr)
-    hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, false, false, true>), dim3(grid), dim3(NT), 0, stream, prm);
+    hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, false, false, 1>), dim3(grid), dim3(NT), 0, stream, prm);
   else if (prm.n_visit_max <= wave_rows_pages<NT, G>())
-    hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, true, false, false>), dim3(grid), dim3(NT), 0, stream, prm);
+    hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, true, false, 0>), dim3(grid), dim3(NT), 0, stream, prm);
   else
-    hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, false, false, false>), dim3(grid), dim3(NT), 0, stream, prm);
+    hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, false, false, 0>), dim3(grid), dim3(NT), 0, stream, prm);
 }
 
 template <int D, int G>
@@ -1771,6 +1785,24 @@ extern "C" se_status se_decode_attend(const se_kv_view* kv, int32_t q_per_kv, co
   return attend_launch(kv, q_per_kv, q, k_new, v_new, new_pos, sel_pages, top_k, scale, max_len,
                        flags, out, lse, logits, logits_stride, ws, ws_bytes, dev_err, stream,
                        nullptr);
+}
+
+// An OmniKV observation layer's attention, for this package's decode driver (not
+// part of sparse_engine.h): se_decode_attend over every slot, and instead of all
+// logits their maximum over the unit's G query heads, group_max fp32
+// [num_units][stride], stride >= max_len.  se_omnikv_select takes it as the logits of
+// groups of one (its score is the maximum over the request's heads either way).
+// A quarter of the bytes at G = 4: writes among a read stream cost far more than
+// their size (256 units of 32768 slots: all logits 889 us, none 663, this 760).
+extern "C" se_status se_observe_attend(const se_kv_view* kv, int32_t q_per_kv, const void* q, const void* k_new,
+                                       const void* v_new, const int32_t* new_pos, float scale, int32_t max_len,
+                                       float* out, float* lse, float* group_max, int32_t stride, void* ws,
+                                       size_t ws_bytes, int32_t* dev_err, hipStream_t stream) {
+  if (group_max == nullptr) return SE_ERR_INVALID_ARGUMENT;
+  AttendParams ex = {};
+  ex.logits_max = 1;
+  return attend_launch(kv, q_per_kv, q, k_new, v_new, new_pos, nullptr, 0, scale, max_len, 0, out, lse, group_max,
+                       stride, ws, ws_bytes, dev_err, stream, &ex);
 }
 
 extern "C" se_status se_decode_step_h2o(const se_kv_view* kv, int32_t q_per_kv, const void* q,

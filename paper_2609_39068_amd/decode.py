@@ -107,9 +107,9 @@ class QuestDecoder:
 
 class OmniKVDecoder:
     """A model's OmniKV decode step, layer by layer (Appendix A.3, OmniKV): an
-    observation layer appends, attends over every slot keeping the logits
-    (se_decode_attend) and selects the b slots with the largest logit over the
-    request's heads (se_omnikv_select); each later layer, until the next
+    observation layer appends, attends over every slot keeping the logits' maximum
+    over each unit's heads and selects the b slots with the largest logit over the
+    request's heads (se_omnikv_select, on groups of one); each later layer, until the next
     observation layer, appends and attends over that selection of its own cache
     (se_attend_slots).  The selection and the buffers are shared by the layers,
     whose calls run one after another on one stream."""
@@ -120,7 +120,7 @@ class OmniKVDecoder:
         self.observe = set(int(l) for l in observation_layers)
         num_req = num_units // num_kv_heads
         self.stride = -(-max_len // 64) * 64
-        self.logits = torch.empty(num_units * q_per_kv * self.stride, dtype=torch.float32, device=device)
+        self.group_max = torch.empty(num_units * self.stride, dtype=torch.float32, device=device)
         self.sel = torch.full((num_req, budget), -1, dtype=torch.int32, device=device)
         na = se.se_workspace_bytes(se.SE_OP_DECODE_ATTEND, num_units, max_len, max_pages, q_per_kv, head_dim, 0)
         ns = se.se_workspace_bytes(se.SE_OP_OMNIKV_SELECT, num_req, max_len, max_pages, q_per_kv, head_dim, 0)
@@ -135,9 +135,9 @@ class OmniKVDecoder:
         observation layer, so that the sparse layers read this step's selection."""
         ml = max_len or self.max_len
         if l in self.observe:
-            se.se_decode_attend(view, self.G, q, k_new, v_new, new_pos, None, 0, self.scale, ml, 0, out, lse,
-                                self.logits, self.stride, self.ws_attend, self.dev_err)
-            se.se_omnikv_select(view, self.G, self.logits, self.stride, self.budget, ml, self.sel,
+            se._observe_attend(view, self.G, q, k_new, v_new, new_pos, self.scale, ml, out, lse, self.group_max,
+                               self.stride, self.ws_attend, self.dev_err)
+            se.se_omnikv_select(view, 1, self.group_max, self.stride, self.budget, ml, self.sel,
                                 self.ws_select, self.dev_err)
             self.selected = True
         else:
