@@ -205,17 +205,17 @@ def quest_step_bytes(L_pre, G, D, top_k):
 def attend_kernel_name(units, n_visit, G, D, quest=False):
     """The decode_attend_kernel instantiation a launch of these sizes runs (the
     library's rule: 1024 threads when the units fit one work-group per compute
-    unit, else 512; per-wavefront rows for the fused steady eviction when the
+    unit and hold more than 48 pages, else 512; per-wavefront rows for the fused steady eviction when the
     largest wavefront slot's share of the pages fits them and every page's
     weights fit the LDS buffer; a Quest step's selection has its own)."""
-    wide = units * -(-n_visit // 1024) <= 256
+    wide = units * -(-n_visit // 1024) <= 256 and (quest or n_visit > 48)
     nt = 1024 if wide else 512
     if quest:
-        return f"decode_attend_kernel<{D},{G},{nt},false,true>"
+        return f"decode_attend_kernel<{D},{G},{nt},false,true,0>"
     rows = (4 * 4 * 5 * 100 - 50) // (34 if wide else 58)
     wbytes = 4 if (nt == 512 and G <= 4) else 2  # fp32 or fp16 weights
     rows = min(rows, 1024, 9216 * 4 // wbytes // (16 * G))
-    return f"decode_attend_kernel<{D},{G},{nt},{'true' if n_visit <= rows else 'false'},false>"
+    return f"decode_attend_kernel<{D},{G},{nt},{'true' if n_visit <= rows else 'false'},false,0>"
 
 
 def snapkv_bytes(L, w, G, D, budget):
@@ -521,7 +521,7 @@ def main_h2o_prefill(args):
                    "retained_before": w.initial_resident - C, "scoring_window": sw, "budget": w.budget,
                    "recent": w.recent, "accumulate": "f32", "parallelism": "none (1 GPU)"},
         "roofline": {"bound": "alu",
-                     "kernel": "se_h2o_prefill_chunk (prefill_norm_kernel + prefill_score_kernel, then the eviction)",
+                     "kernel": "se_h2o_prefill_chunk (window_norm_kernel + window_score_kernel, then the eviction)",
                      "achieved": round(alu_achieved, 2), "peak": VALU_PEAK_TSLOTS,
                      "unit": "T VALU lane-slots/s", "frac": round(alu_achieved / VALU_PEAK_TSLOTS, 4),
                      "traffic": read_traffic(PREFILL_TRAFFIC_SUMMARY, SNAPKV_SOURCES),
@@ -756,8 +756,8 @@ def main_prune(args):
 
 def omnikv_layer_bytes(L, G, D, b, observe):
     """Bytes one layer's OmniKV decode call(s) must move for units with L slots
-    after the append.  Observation layer (se_decode_attend with logits, then
-    se_omnikv_select): every slot's K and V rows and its G logits written, then
+    after the append.  Observation layer (attention, then se_omnikv_select):
+    every slot's K and V rows and its largest logit over the group written, then
     read back, plus per request the max score written and read and the
     selection written.  Sparse layer (se_attend_slots): the b selected K and V
     rows.  Both: the G query rows, G output rows and lse, and the append (k, v
@@ -767,7 +767,7 @@ def omnikv_layer_bytes(L, G, D, b, observe):
     units = int(L.shape[0])
     per_unit = G * D * 2 + G * D * 4 + G * 4 + 2 * D * 2 * 2 + 4
     if observe:
-        return int(L.sum()) * (2 * D * 2 + 2 * G * 4) + units * per_unit
+        return int(L.sum()) * (2 * D * 2 + 2 * 4) + units * per_unit
     return units * (int(b) * 2 * D * 2 + per_unit)
 
 
