@@ -65,6 +65,7 @@ struct AttendParams {
   int32_t n_visit_max;
   int32_t pps;
   int32_t n_split;
+  int32_t exact_weights;  // the score update's weights stay fp32
   int32_t accumulate;
   float* out;
   float* lse;
@@ -983,7 +984,9 @@ __device__ __forceinline__ const int* fused_quest_select(const AttendParams& p, 
 // the step's length bound, since carrying both paths costs the shorter one
 // registers.
 // kLogits: 1: every slot's logits are an output; 2: their maximum over the group.
-template <int D, int G, int NT, bool kWaveRows, bool kQuest, int kLogits>
+// kF32: fp32 weights in LDS whatever WeightT says (pages past the buffer go to
+// the workspace, fp32 too).
+template <int D, int G, int NT, bool kWaveRows, bool kQuest, int kLogits, bool kF32 = false>
 __global__ __launch_bounds__(NT, 4) void decode_attend_kernel(const AttendParams p) {
   constexpr int NW = NT / kWave;  // wavefronts per work-group
   using LN = Lanes<D>;
@@ -1006,7 +1009,7 @@ __global__ __launch_bounds__(NT, 4) void decode_attend_kernel(const AttendParams
   __shared__ uint32_t lds_q[G][D / 2];  // the unit's G query rows (bf16 pairs)
   __shared__ float lds_w[kWeightCap];    // per-slot weights, then the eviction's holes
   __shared__ float lds_mr[kWeightMrCap];
-  using W = WeightT<NT, kWaveRows, G>;
+  using W = typename std::conditional<kF32, float, WeightT<NT, kWaveRows, G>>::type;
   W* const lds_wh = reinterpret_cast<W*>(lds_w);
   SE_EVICT_SCRATCH_WITH_HOLES(NT, esc, reinterpret_cast<int*>(lds_w));
   __shared__ int lds_scan[NT / kWave + 1];
@@ -1619,6 +1622,8 @@ static void launch_attend_nt(const AttendParams& prm, int grid, hipStream_t stre
     hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, false, false, 2>), dim3(grid), dim3(NT), 0, stream, prm);
   else if (prm.logits != nullptr)
     hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, false, false, 1>), dim3(grid), dim3(NT), 0, stream, prm);
+  else if (prm.exact_weights && !(std::is_same<WeightT<NT, true, G>, float>::value && prm.n_visit_max <= wave_rows_pages<NT, G>()))
+    hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, false, false, 0, true>), dim3(grid), dim3(NT), 0, stream, prm);
   else if (prm.n_visit_max <= wave_rows_pages<NT, G>())
     hipLaunchKernelGGL((decode_attend_kernel<D, G, NT, true, false, 0>), dim3(grid), dim3(NT), 0, stream, prm);
   else
@@ -1739,6 +1744,10 @@ static se_status attend_launch(const se_kv_view* kv, int32_t q_per_kv, const voi
   prm.pps = s.pps;
   prm.n_split = s.n_split;
   prm.accumulate = accumulate ? 1 : 0;
+  // Where splits would use the chip's idle places (their weights wait in the
+  // workspace, fp32) but a whole unit is faster, its weights stay fp32 as well;
+  // launches that fill the places with whole units keep them fp16.
+  prm.exact_weights = s.n_split == 1 && kv->num_units < 512 && kv->num_units != 256 ? 1 : 0;
   prm.out = out;
   prm.lse = lse;
   prm.logits = logits;

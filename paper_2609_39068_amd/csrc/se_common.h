@@ -64,7 +64,8 @@ inline SplitShape split_shape(int num_units, int n_visit, int resident = 512) {
   const int lo = (int)ceil_div(n_visit, max_group_pages);
   int hi = (int)ceil_div(resident, num_units);
   hi = hi < (int)ceil_div(n_visit, min_pages) ? hi : (int)ceil_div(n_visit, min_pages);
-  hi = hi > 2 * lo ? hi : 2 * lo;
+  const int fuller = lo + (lo < 8 ? lo : 8);  // a few more than the least, for fuller rounds
+  hi = hi > fuller ? hi : fuller;
   int splits = lo;
   int64_t best = INT64_MAX;
   for (int n = lo; n <= hi; ++n) {
