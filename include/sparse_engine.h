@@ -221,8 +221,11 @@ se_status se_decode_step_h2o(const se_kv_view* kv, int32_t q_per_kv, const void*
  * process ends.  The call allocates nothing; the first call on a device looks
  * up that device's copy of the array.
  *  Arguments as for se_decode_step_h2o without ws / ws_bytes.
- *  Returns SE_ERR_WORKSPACE when se_workspace_bytes(SE_OP_DECODE_ATTEND,
- *  num_units, max_len, max_pages, q_per_kv, head_dim, 0) exceeds the array
+ *  Returns SE_ERR_WORKSPACE when the step's workspace with the fewest work-groups
+ *  per unit exceeds the array; where se_workspace_bytes(SE_OP_DECODE_ATTEND,
+ *  num_units, max_len, max_pages, q_per_kv, head_dim, 0) exceeds it by the
+ *  partials of more work-groups alone, the step takes the fewest (sums in another
+ *  order than the step with a workspace of its own)
  *  (for example 512 units of 32769 slots need 289 MB; a steady 4096-slot step
  *  of 2048 units needs 147 MB).  Every call on one GPU shares the array, so
  *  calls that may overlap on one GPU (different streams, or concurrent host

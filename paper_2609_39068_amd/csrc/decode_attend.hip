@@ -1716,7 +1716,12 @@ static se_status attend_launch(const se_kv_view* kv, int32_t q_per_kv, const voi
   const int D = kv->head_dim;
   const int n_visit = attend_n_visit(max_len, kv->max_pages, top_k);
   const bool wide = attend_wide(kv->num_units, n_visit) && (sel_pages != nullptr || n_visit > kNarrowPages);
-  const SplitShape s = split_shape(kv->num_units, n_visit, wide ? 256 : 512);
+  SplitShape s = split_shape(kv->num_units, n_visit, wide ? 256 : 512);
+  // A few more pages can take fewer splits, so that a workspace sized for a longer
+  // bound (or the static array) may be short of this one's partials by some
+  // percent.  The fewest splits fit every workspace of a bound as long as this one.
+  if (ws_bytes < attend_ws_layout(kv->num_units, s, q_per_kv, D).total)
+    s = split_shape(kv->num_units, n_visit, wide ? 256 : 512, true);
   const AttendWs lay = attend_ws_layout(kv->num_units, s, q_per_kv, D);
   if (ws == nullptr || ws_bytes < lay.total) return SE_ERR_WORKSPACE;
 
@@ -1877,8 +1882,11 @@ extern "C" se_status se_decode_step_h2o_noalloc(const se_kv_view* kv, int32_t q_
   se_status st = check_view(kv);
   if (st != SE_OK) return st;
   if (max_len <= 0) return SE_ERR_INVALID_ARGUMENT;
-  const size_t need = se_attend_workspace_bytes(kv->num_units, max_len, kv->max_pages, q_per_kv, kv->head_dim, 0);
-  if (need > kStaticScratchBytes) return SE_ERR_WORKSPACE;
+  if (kv->num_units > 0 && kv->max_pages > 0 && q_per_kv > 0) {
+    const int n_visit = attend_n_visit(max_len, kv->max_pages, 0);
+    const SplitShape s = split_shape(kv->num_units, n_visit, attend_wide(kv->num_units, n_visit) ? 256 : 512, true);
+    if (attend_ws_layout(kv->num_units, s, q_per_kv, kv->head_dim).total > kStaticScratchBytes) return SE_ERR_WORKSPACE;
+  }
   void* ws = nullptr;
   st = static_scratch(&ws);
   if (st != SE_OK) return st;

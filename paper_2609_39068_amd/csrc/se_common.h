@@ -56,7 +56,8 @@ struct SplitShape {
 // streams some kWorthPages pages in: 8 units of 65 pages take 20.5 us whole and
 // 22.5 split, of 129 pages 29.8 whole and 23.8 split, 128 units of 129 pages 46.6
 // and 43.9.
-inline SplitShape split_shape(int num_units, int n_visit, int resident = 512) {
+// fewest: as few splits as the page table in LDS allows.
+inline SplitShape split_shape(int num_units, int n_visit, int resident = 512, bool fewest = false) {
   const int min_pages = 16;          // at least two pages per wavefront
   const int max_group_pages = 1024;  // the page table a work-group stages in LDS
   const int kFixedPages = 16;
@@ -65,7 +66,7 @@ inline SplitShape split_shape(int num_units, int n_visit, int resident = 512) {
   int hi = (int)ceil_div(resident, num_units);
   hi = hi < (int)ceil_div(n_visit, min_pages) ? hi : (int)ceil_div(n_visit, min_pages);
   const int fuller = lo + (lo < 8 ? lo : 8);  // a few more than the least, for fuller rounds
-  hi = hi > fuller ? hi : fuller;
+  hi = fewest ? lo : hi > fuller ? hi : fuller;
   int splits = lo;
   int64_t best = INT64_MAX;
   for (int n = lo; n <= hi; ++n) {

@@ -1,0 +1,50 @@
+"""A workspace sized for a longer bound serves every shorter step, also where the
+shorter bound's own shape would split its units further and need more."""
+import numpy as np
+import pytest
+import torch
+
+from workloads import isolated_units, to_device
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def se():
+    import paper_2609_39068_amd as m
+    assert torch.cuda.is_available()
+    return m
+
+
+@pytest.mark.parametrize("units,G,d,pages,sized_for", [
+    (16, 1, 64, 256, 257),   # whole units then: the epilogue of one work-group
+    (2, 1, 64, 2047, 2049),  # the fewest: two splits
+    (4, 1, 64, 1024, 1025),
+])
+def test_workspace_of_a_longer_bound(se, units, G, d, pages, sized_for):
+    print(f"units={units} G={G} d={d} pages={pages}", flush=True)
+    L = 16 * pages
+    st = to_device(isolated_units([L - 17 * (u % 2) for u in range(units)], max_pages=sized_for, head_dim=d, seed=pages,
+                                  num_kv_heads=units), DEV)
+    view = se.KVView(st.kv_pool, st.pos_pool, st.score_pool, None, st.block_table, st.lengths, num_kv_heads=units)
+    need = se.se_workspace_bytes(se.SE_OP_DECODE_ATTEND, units, L, sized_for, G, d, 0)
+    have = se.se_workspace_bytes(se.SE_OP_DECODE_ATTEND, units, 16 * sized_for, sized_for, G, d, 0)
+    assert have < need  # the case this test is for
+    q = torch.randn(1, units * G, d, generator=torch.Generator().manual_seed(3)).to(torch.bfloat16).to(DEV)
+    start = st.score_pool.clone()
+    err = torch.zeros(1, dtype=torch.int32, device=DEV)
+    got = []
+    for nbytes in (need, have):
+        st.score_pool.copy_(start)
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+        out, lse = torch.zeros(1, units * G, d, device=DEV), torch.zeros(1, units * G, device=DEV)
+        se.se_decode_attend(view, G, q, None, None, None, None, 0, float(np.float32(1 / np.sqrt(d))), L,
+                            se.SE_ATTEND_ACCUMULATE, out, lse, None, 0, ws, err)
+        torch.cuda.synchronize()
+        got.append((out.double(), lse.double(), st.score_pool.double()))
+    assert se.se_read_device_errors(err) == 0
+    for name, a, b in zip(("out", "lse", "score"), *got):
+        # fp32 sums of the same terms in another order, each at most 32752 of them: well under 1e-5 in the 2-norm
+        assert float((a - b).norm() / a.norm()) < 1e-5, name
